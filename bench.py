@@ -43,8 +43,8 @@ COPY_BYTES = 1 << 30   # calibration copy: 1 GiB read + 1 GiB written
 KERNEL_NAMES = {"fx": "k_fx", "fy": "k_fy", "fz": "k_fz", "contract": "k_contract_bis_reg"}
 # midpoint P_l: forward passes, product + inverse z pass, inverse y/x passes, re-weighting, the
 # forward passes of the A fields and the k-space contraction
-KERNEL_NAMES_MID = {"fx": "k_fx", "fy": "k_fy", "fziz": "k_fziz", "iy": "k_fy", "ix": "k_ix", "ix_bin": "k_ix",
-                    "reweight": "k_reweight", "afx": "k_fx", "afy": "k_fy", "afz": "k_fz",
+KERNEL_NAMES_MID = {"fx": "k_fx", "fy": "k_fy", "fziz": "k_fziz", "iy": "k_fy", "ix_bin": "k_ix",
+                    "mix": "k_mix", "afy": "k_fy", "afz": "k_fz",
                     "contract": "k_contract_mid"}
 # bisector xi_l: forward passes, per-mode targets, inverse z / y passes, c2r x pass with r-binning
 KERNEL_NAMES_BXI = {"fx": "k_fx", "fy": "k_fy", "fz": "k_fz", "targets": "k_targets", "iz": "k_iz",

@@ -17,7 +17,9 @@ ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libpw.so")
 BUILD_DIR = os.path.join(HERE, "_build")
 
-SOURCES = ["generated.hip", "kernels.hip", "inverse.hip", "paint.hip", "coeffs.cpp", "plan.cpp", "api.cpp"]
+# mix.hip is built once per mesh size (its generated shapes compile side by side)
+MIX = [f"mix.hip@{n}" for n in (256, 512, 128, 64, 32, 16)]
+SOURCES = MIX + ["generated.hip", "kernels.hip", "inverse.hip", "paint.hip", "coeffs.cpp", "plan.cpp", "api.cpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
@@ -33,17 +35,25 @@ def _deps_mtime() -> float:
     """Newest mtime of the headers every translation unit may include."""
     paths = [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".h")]
     paths += [os.path.join(ROOT, "include", "pw.h"), os.path.join(BUILD_DIR, "contract_gen.inc"),
+              os.path.join(BUILD_DIR, "mix_gen.inc"),
               os.path.abspath(__file__)]  # compile flags live here
     return max(os.path.getmtime(p) for p in paths if os.path.exists(p))
 
 
+def _source(src: str):
+    """(source file, its own compile flags) of an entry of SOURCES."""
+    name, _, mesh = src.partition("@")
+    return name, [f"-DPW_MIX_N={mesh}"] if mesh else []
+
+
 def _compile(src: str, incremental: bool = False) -> str:
-    obj = os.path.join(BUILD_DIR, os.path.basename(src) + ".o")
+    obj = os.path.join(BUILD_DIR, src.replace("@", "_") + ".o")
+    src, flags = _source(src)
     if incremental and os.path.exists(obj):
         newest = max(os.path.getmtime(os.path.join(CSRC, src)), _deps_mtime())
         if os.path.getmtime(obj) > newest:
             return obj
-    cmd = [HIPCC] + COMMON + ["-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [HIPCC] + COMMON + flags + ["-c", os.path.join(CSRC, src), "-o", obj]
     if src.endswith(".cpp"):
         cmd = [HIPCC] + COMMON + ["-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
@@ -60,16 +70,16 @@ def _generate():
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"generator build failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
-    out = os.path.join(BUILD_DIR, "contract_gen.inc")
-    tmp = out + ".new"
-    r = subprocess.run([exe, tmp], capture_output=True, text=True)
+    outs = [os.path.join(BUILD_DIR, f) for f in ("contract_gen.inc", "mix_gen.inc")]
+    r = subprocess.run([exe] + [o + ".new" for o in outs], capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"generator failed\n{r.stdout}\n{r.stderr}")
-    # keep the old file (and its mtime) when nothing changed
-    if os.path.exists(out) and open(out).read() == open(tmp).read():
-        os.remove(tmp)
-    else:
-        os.replace(tmp, out)
+    for out in outs:
+        # keep the old file (and its mtime) when nothing changed
+        if os.path.exists(out) and open(out).read() == open(out + ".new").read():
+            os.remove(out + ".new")
+        else:
+            os.replace(out + ".new", out)
 
 
 def build(jobs: int | None = None, verbose: bool = False, incremental: bool = False) -> str:
@@ -124,13 +134,14 @@ def build_sanitized(jobs: int | None = None) -> str:
     os.makedirs(SAN_DIR, exist_ok=True)
     os.makedirs(BUILD_DIR, exist_ok=True)
     _generate()
-    newest = max([_deps_mtime()] + [os.path.getmtime(os.path.join(CSRC, f)) for f in SOURCES])
+    newest = max([_deps_mtime()] + [os.path.getmtime(os.path.join(CSRC, _source(f)[0])) for f in SOURCES])
 
     def one(src):
-        obj = os.path.join(SAN_DIR, os.path.basename(src) + ".o")
+        obj = os.path.join(SAN_DIR, src.replace("@", "_") + ".o")
+        src, flags = _source(src)
         if os.path.exists(obj) and os.path.getmtime(obj) > newest:
             return obj
-        cmd = [HIPCC] + SAN_FLAGS + ["-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = [HIPCC] + SAN_FLAGS + flags + ["-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:
             raise RuntimeError(f"compile failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")

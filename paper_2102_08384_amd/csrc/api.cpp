@@ -475,7 +475,6 @@ std::unique_ptr<DevPlan> build_dev_plan(pw_ctx *ctx, const pw_config *cfg, char 
     }
     dp->jobs = upload(M, h.jobs);
     dp->ijobs = upload(M, h.ijobs);
-    dp->ajobs = upload(M, h.ajobs);
     auto up_prune = [&](const Prune &p, DevPrune &d) {
       d.ycnt = upload(M, p.ycnt);
       d.yoff = upload(M, p.yoff);
@@ -1028,29 +1027,22 @@ DevPlan *launch_estimate(pw_ctx *ctx, Lane &ln, const pw_config *cfg, const pw_c
     if (xi) {
       // a8: c2r along x fused with the |D|^alpha y(D^) weighting and FP64 r-binning
       mark("ix_bin", ypart);
-      launch_ix(s, h.prec, N, 1, yout, nullptr, F.rs, dp->ijobs, (int)h.ijobs.size(), dp->icoef, h.nell, h.nz, h.ny,
+      launch_ix(s, h.prec, N, yout, F.rs, dp->ijobs, (int)h.ijobs.size(), dp->icoef, h.nell, h.nz, h.ny,
                 dp->zidx, dp->yidx, h.H, h.unit, inv_n3, dp->bin_of_s2, n_s2, h.n_bins, dp->acc, dp->tw);
       mark("finalize", 0.0);
       launch_finalize_xi(s, dp->acc, h.nell, h.n_bins, h.H * h.H * h.H, dp->norm, dp->out);
     } else {
       void *Aoff = A + (size_t)h.n_inplace * sfull_b;  // behind the alpha = 0 products
       if (h.n_inv > 0) {
-        // g fields in real space (Aoff), then a6: A_{l nu} = sum Phi' y(D^) |D|^alpha g (into B)
-        mark("ix", ypart + (double)h.n_inv * ncell * rsz);
-        launch_ix(s, h.prec, N, 0, yout, Aoff, F.rs, dp->ijobs, (int)h.ijobs.size(), nullptr, h.nell, h.nz, h.ny,
-                  dp->zidx, dp->yidx, h.H, h.unit, inv_n3, nullptr, 0, 0, nullptr, dp->tw);
-        mark("reweight", (double)(h.n_inv + h.n_a) * ncell * rsz);
-        launch_reweight(s, h.prec, N, h.ell_max, h.order, h.all_parity, Aoff, B, h.H / h.unit);
-        // forward transforms of A, pruned to the k-sphere of the bins (ending in Aoff)
+        // a6: the g fields' inverse x pass, A_{l nu} = sum Phi' y(D^) |D|^alpha g and the forward x
+        // pass of A in one kernel, then A's y and z passes, pruned to the k-sphere of the bins
+        // (ending in Aoff)
         const Prune &P = h.sph;
         const double a1 = (double)h.n_a * N * N * P.nkx * csz, a2 = (double)h.n_a * N * P.npen * csz,
                      a3 = (double)h.n_a * P.nretained * csz;
-        mark("afx", (double)h.n_a * ncell * rsz + a1);
-        tuned_launch(ctx, ln, tune_key("fx", h, (int)h.ajobs.size(), FX_PLAIN, P.nkx), fx_candidates(h.prec, N),
-                     [&](ColTune t) {
-                       launch_fx(s, h.prec, N, FX_PLAIN, B, Aoff, dp->ajobs, (int)h.ajobs.size(), P.nkx, P.rs,
-                                 cfg->box_origin, h.H, h.unit, dp->tw, nullptr, nullptr, nullptr, t);
-                     });
+        mark("mix", ypart + a1);
+        launch_mix(s, h.prec, N, h.ell_max, h.order, h.all_parity, yout, Aoff, F.rs, P.nkx, P.rs, inv_n3,
+                   h.H / h.unit, dp->tw);
         mark("afy", a1 + a2);
         if (P.npen > 0)
           launch_fy(s, h.prec, N, 0, Aoff, B, h.n_a, N, P.nkx, P.rs, dp->sph.ycnt, dp->sph.yoff, P.npen, dp->tw,

@@ -35,6 +35,9 @@ std::vector<Term> midpoint_terms_all(int ell_max, int alpha);
 // Parity-even Legendre coefficients F^{alpha,l}_J (Appendix E).
 double legendre_F(int alpha, int l, int J);
 
+// g fields per step of the midpoint P_l row pass (eight pair transforms side by side)
+constexpr int kMixFields = 16;
+
 // Building blocks (exposed for the table self-checks).
 double wigner3j(int j1, int j2, int j3, int m1, int m2, int m3);
 double gaunt(int l1, int l2, int l3, int m1, int m2, int m3);

@@ -226,6 +226,53 @@ __device__ __forceinline__ void buf_store(cplx<R> x, __amdgpu_buffer_rsrc_t r, u
   }
 }
 
+// LDS ordering between the lanes of one wavefront (LDS executes a wavefront's instructions in
+// order; this keeps the compiler from moving accesses across the exchange point).
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// value of lane `src` (0..63) of this wavefront
+template <typename R>
+__device__ __forceinline__ cplx<R> lane_fetch(int src, cplx<R> v) {
+  const int addr = src << 2;
+  if constexpr (sizeof(R) == 4) {
+    return mk<R>(__int_as_float(__builtin_amdgcn_ds_bpermute(addr, __float_as_int(v.x))),
+                 __int_as_float(__builtin_amdgcn_ds_bpermute(addr, __float_as_int(v.y))));
+  } else {
+    const long long xb = __double_as_longlong(v.x), yb = __double_as_longlong(v.y);
+    const int xl = __builtin_amdgcn_ds_bpermute(addr, (int)(xb & 0xffffffffLL));
+    const int xh = __builtin_amdgcn_ds_bpermute(addr, (int)(xb >> 32));
+    const int yl = __builtin_amdgcn_ds_bpermute(addr, (int)(yb & 0xffffffffLL));
+    const int yh = __builtin_amdgcn_ds_bpermute(addr, (int)(yb >> 32));
+    return mk<R>(__longlong_as_double(((long long)xh << 32) | (unsigned)xl),
+                 __longlong_as_double(((long long)yh << 32) | (unsigned)yl));
+  }
+}
+
+// Loads and stores of streams that nothing re-reads soon (no place kept in the caches)
+template <typename C> __device__ __forceinline__ C load_nt(const C *p) {
+  C x;
+  if constexpr (sizeof(C) == 8) {
+    const f32x2 v = __builtin_nontemporal_load(reinterpret_cast<const f32x2 *>(p));
+    x.x = v.x; x.y = v.y;
+  } else {
+    const f64x2 v = __builtin_nontemporal_load(reinterpret_cast<const f64x2 *>(p));
+    x.x = v.x; x.y = v.y;
+  }
+  return x;
+}
+
+// fn(std::integral_constant<int, 0>), .., fn(std::integral_constant<int, COUNT - 1>), in order
+template <int COUNT, int I = 0, typename Fn> __device__ __forceinline__ void for_each_const(Fn &&fn) {
+  if constexpr (I < COUNT) {
+    fn(std::integral_constant<int, I>());
+    for_each_const<COUNT, I + 1>(fn);
+  }
+}
+
 // Groups of fields per block (grid.y) for column passes, so that a launch has about 4096
 // blocks when the pencil dimension alone gives fewer.
 inline int field_groups(int nfields, int nblocks_other) {

@@ -5,17 +5,17 @@
 //   targets(a, T)     T_{l nu} = sum S Re(conj(a_p1) a_p2)               (one k mode)
 //   run_orders(a, w, E)  E_{beta, l} += sum_nu w_{l nu} sum S^beta Re(conj(a_p1) a_p2): the
 //                     terms of each order theta^(2 beta) into an accumulator of their own
-// MidReweight<L, K, R> (midpoint parity-even, Appendix D coefficients in the real basis):
-//   run(g, yD, Dp, A) A_{l nu} = sum_{alpha>0} sum Phi' y_J1^mu1(D^) |D|^alpha g_{alpha J2 mu2}
-//   with g indexed by the canonical midpoint field order (alpha = 2, 4, .., K; J even
-//   <= L + alpha; mu = -J .. J), yD by J1*J1 + J1 + mu1, Dp[alpha/2] = |D|^alpha and A by the
-//   order l = 2, 4, .., L; nu = -l .. l.  The monopole has no alpha > 0 term.
-// MidReweightAll<L, K, R> (midpoint all-parity, Section 3.2: phi in the real basis with the
-//   sign (-1)^J2 of g folded in): the same run(g, yD, Dp, A) with every alpha = 1 .. K, g in
-//   the canonical all-parity order (alpha = 1 .. K; J = alpha mod 2, +2, .. <= L + alpha;
-//   mu = -J .. J), yD holding every J1 <= K (odd too) and Dp[alpha] = |D|^alpha.
+// MidReweight<L, K, ALLP, R> (midpoint; parity-even: Appendix D coefficients in the real basis,
+//   all-parity: Section 3.2's phi with the sign (-1)^J2 of g folded in):
+//   dirs(x, y, z, yD)   y_J1^mu1 of a unit vector at yD[J1*J1 + J1 + mu1], J1 <= K (parity-even: even J1)
+//   chunk<C>(g, yD, Dp, A)  A_{l nu} += sum_{alpha>0} sum Phi' y_J1^mu1(D^) |D|^alpha g_{alpha J2 mu2} over
+//   the g fields [kMixFields * C, kMixFields * (C + 1)) of the canonical order, g their values.
+//   The canonical order is (alpha, J, mu): alpha = 2, 4, .., K with J even <= L + alpha, or every
+//   alpha = 1 .. K with J = alpha mod 2, +2, .. <= L + alpha; Dp[alpha / 2] (all-parity: Dp[alpha])
+//   is |D|^alpha and A runs over l = 2, 4, .., L; nu = -l .. l.  The monopole has no alpha > 0 term.
 // Every coupling value comes from the host FP64 generator as a literal.
-// Usage: gen_contract <output.inc>
+// Usage: gen_contract <contract_gen.inc> <mix_gen.inc>
+#include <cmath>
 #include <cstdio>
 #include <map>
 #include <utility>
@@ -25,40 +25,16 @@
 
 namespace {
 
-int mid_field_index(int L, int K, int alpha, int J, int mu) {
-  int p = 0;
-  for (int a = 2; a <= K; a += 2)
-    for (int j = 0; j <= L + a; j += 2)
-      for (int m = -j; m <= j; ++m) {
-        if (a == alpha && j == J && m == mu) return p;
-        ++p;
-      }
-  return -1;
-}
-
-int mid_nfields(int L, int K) {
-  int p = 0;
-  for (int a = 2; a <= K; a += 2)
-    for (int j = 0; j <= L + a; j += 2) p += 2 * j + 1;
-  return p;
-}
-
-int mid_all_field_index(int L, int K, int alpha, int J, int mu) {
-  int p = 0;
-  for (int a = 1; a <= K; ++a)
+// g fields of the midpoint P_l in the canonical order
+struct GField {
+  int alpha, J, mu;
+};
+std::vector<GField> mid_fields(int L, int K, bool all) {
+  std::vector<GField> v;
+  for (int a = all ? 1 : 2; a <= K; a += all ? 1 : 2)
     for (int j = a % 2; j <= L + a; j += 2)
-      for (int m = -j; m <= j; ++m) {
-        if (a == alpha && j == J && m == mu) return p;
-        ++p;
-      }
-  return -1;
-}
-
-int mid_all_nfields(int L, int K) {
-  int p = 0;
-  for (int a = 1; a <= K; ++a)
-    for (int j = a % 2; j <= L + a; j += 2) p += 2 * j + 1;
-  return p;
+      for (int m = -j; m <= j; ++m) v.push_back(GField{a, j, m});
+  return v;
 }
 
 int a_index(int l, int nu) {  // l = 2, 4, ...
@@ -67,16 +43,106 @@ int a_index(int l, int nu) {  // l = 2, 4, ...
   return p + nu + l;
 }
 
+// Straight-line evaluation of the real harmonics y_J^mu(x, y, z), J <= K (even J only unless
+// `all`), by the Cartesian recurrences
+//   Q_m^m = 1, Q_J^m = (2J-1)/(J-m) z Q_{J-1}^m - (J+m-1)/(J-m) Q_{J-2}^m,
+//   y_J^{+-m} = norm_Jm Q_J^m(z) {Re, Im} (x + i y)^m.
+void emit_dirs(FILE *f, int K, bool all) {
+  std::fprintf(f, "  __device__ __forceinline__ static void dirs(R x, R y, R z, R *yD) {\n");
+  std::fprintf(f, "    const R c0 = (R)1, s0 = (R)0;\n");
+  for (int m = 1; m <= K; ++m)
+    std::fprintf(f, "    const R c%d = c%d * x - s%d * y, s%d = c%d * y + s%d * x;\n", m, m - 1, m - 1, m, m - 1, m - 1);
+  for (int m = 0; m <= K; ++m)
+    for (int J = m; J <= K; ++J) {
+      if (J == m) std::fprintf(f, "    const R q%d_%d = (R)1;\n", J, m);
+      else if (J == m + 1) std::fprintf(f, "    const R q%d_%d = (R)%d * z;\n", J, m, 2 * m + 1);
+      else
+        std::fprintf(f, "    const R q%d_%d = (R)%.17g * z * q%d_%d - (R)%.17g * q%d_%d;\n", J, m,
+                     (2.0 * J - 1) / (J - m), J - 1, m, (J + m - 1.0) / (J - m), J - 2, m);
+      if (!all && (J & 1)) continue;
+      double ratio = 1.0, dfm = 1.0;  // (J-m)!/(J+m)! and (2m-1)!!
+      for (int i = J - m + 1; i <= J + m; ++i) ratio /= (double)i;
+      for (int i = 2 * m - 1; i > 1; i -= 2) dfm *= (double)i;
+      const double nrm = std::sqrt((2.0 * J + 1) / (4.0 * 3.14159265358979323846) * ratio) * dfm *
+                         (m > 0 ? std::sqrt(2.0) : 1.0);
+      if (m == 0) std::fprintf(f, "    yD[%d] = (R)%.17g * q%d_%d;\n", J * J + J, nrm, J, m);
+      else
+        std::fprintf(f, "    yD[%d] = ((R)%.17g * q%d_%d) * c%d; yD[%d] = ((R)%.17g * q%d_%d) * s%d;\n", J * J + J + m,
+                     nrm, J, m, m, J * J + J - m, nrm, J, m, m);
+    }
+  std::fprintf(f, "  }\n");
+}
+
+// MidReweight<L, K, all>; false on an inconsistent field set.
+bool emit_mid(FILE *f, int L, int K, bool all) {
+  const std::vector<GField> fields = mid_fields(L, K, all);
+  std::map<std::pair<int, std::pair<int, int>>, int> at;
+  for (size_t i = 0; i < fields.size(); ++i) at[{fields[i].alpha, {fields[i].J, fields[i].mu}}] = (int)i;
+  const int NG = (int)fields.size(), NCH = (NG + pw::kMixFields - 1) / pw::kMixFields;
+  int NA = 0;
+  for (int l = 2; l <= L; l += 2) NA += 2 * l + 1;
+  std::fprintf(f, "template <typename R> struct MidReweight<%d, %d, %s, R> {\n", L, K, all ? "true" : "false");
+  std::fprintf(f, "  static constexpr bool kGenerated = true;\n");
+  std::fprintf(f, "  static constexpr int NG = %d, NA = %d, NCH = %d;\n", NG, NA, NCH);
+  emit_dirs(f, K, all);
+  // chunk -> (Dp index, J1 mu1 index) -> local g index -> [(coef, A index)]: one weighted value at a
+  // time is live, and every term is one multiply-add into its A
+  typedef std::map<int, std::vector<std::pair<double, int>>> Users;
+  std::vector<std::map<std::pair<int, int>, Users>> by((size_t)NCH);
+  for (int alpha = all ? 1 : 2; alpha <= K; alpha += all ? 1 : 2)
+    for (const pw::Term &t : all ? pw::midpoint_terms_all(L, alpha) : pw::midpoint_terms(L, alpha)) {
+      if (t.l == 0) {
+        // the monopole carries no line-of-sight dependence: its alpha > 0 couplings vanish
+        if (t.c > 1e-12 || t.c < -1e-12) {
+          std::fprintf(stderr, "gen_contract: non-zero monopole coupling at alpha=%d\n", alpha);
+          return false;
+        }
+        continue;
+      }
+      auto it = at.find({alpha, {t.J2, t.mu2}});
+      if (it == at.end()) {
+        std::fprintf(stderr, "gen_contract: field (alpha=%d, J=%d, mu=%d) outside the field set\n", alpha, t.J2, t.mu2);
+        return false;
+      }
+      const int p = it->second;
+      by[(size_t)(p / pw::kMixFields)][{all ? alpha : alpha / 2, pw::sh_index(t.J1, t.mu1)}][p % pw::kMixFields]
+          .push_back({t.c, a_index(t.l, t.nu)});
+    }
+  std::fprintf(f, "  template <int C> __device__ __forceinline__ static void chunk(const R *g, const R *yD, const R *Dp, R *A) {\n");
+  for (int c = 0; c < NCH; ++c) {
+    std::fprintf(f, "    if constexpr (C == %d) {\n", c);
+    for (auto &grp : by[(size_t)c]) {
+      std::fprintf(f, "      {\n        const R w = yD[%d] * Dp[%d];\n", grp.first.second, grp.first.first);
+      for (auto &gi : grp.second) {
+        std::fprintf(f, "        { const R h = w * g[%d];", gi.first);
+        for (auto &ca : gi.second) std::fprintf(f, " A[%d] += (R)%.17g * h;", ca.second, ca.first);
+        std::fprintf(f, " }\n");
+      }
+      std::fprintf(f, "      }\n");
+    }
+    std::fprintf(f, "    }\n");
+  }
+  std::fprintf(f, "  }\n};\n");
+  return true;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
-  if (argc < 2) {
-    std::fprintf(stderr, "usage: gen_contract <out.inc>\n");
+  if (argc < 3) {
+    std::fprintf(stderr, "usage: gen_contract <contract.inc> <mix.inc>\n");
     return 2;
   }
   FILE *f = std::fopen(argv[1], "w");
   if (!f) return 1;
   std::fprintf(f, "// Generated by gen_contract.cpp at build time; do not edit.\n");
+  // (L, K, all-parity) of the midpoint P_l
+  const struct {
+    int L, K;
+    bool all;
+  } mid_shapes[] = {{2, 2, false}, {2, 4, false}, {2, 6, false}, {4, 2, false}, {4, 4, false}, {4, 6, false},
+                    {6, 2, false}, {6, 4, false}, {2, 1, true},  {2, 2, true},  {2, 3, true},  {2, 4, true},
+                    {4, 1, true},  {4, 2, true},  {4, 3, true},  {4, 4, true}};
   const int lmaxs[] = {0, 2, 4, 6};
   for (int L : lmaxs)
     for (int B = 0; B <= 2; ++B) {
@@ -129,96 +195,19 @@ int main(int argc, char **argv) {
       std::fprintf(f, "  }\n");
       std::fprintf(f, "};\n");
     }
-  const int mid_shapes[][2] = {{2, 2}, {2, 4}, {2, 6}, {4, 2}, {4, 4}, {4, 6}, {6, 2}, {6, 4}};
-  for (const auto &shape : mid_shapes) {
-    const int L = shape[0], K = shape[1];
-    const int NG = mid_nfields(L, K);
-    int NA = 0;
-    for (int l = 2; l <= L; l += 2) NA += 2 * l + 1;
-    std::fprintf(f, "template <typename R> struct MidReweight<%d, %d, R> {\n", L, K);
-    std::fprintf(f, "  static constexpr bool kGenerated = true;\n");
-    std::fprintf(f, "  static constexpr int NG = %d;\n  static constexpr int NA = %d;\n", NG, NA);
-    std::fprintf(f, "  __device__ __forceinline__ static void run(const R *g, const R *yD, const R *Dp, R *A) {\n");
-    // (l, nu) -> (J1 mu1 index, alpha) -> [(coef, g index)]
-    std::map<std::pair<int, int>, std::map<std::pair<int, int>, std::vector<std::pair<double, int>>>> by;
-    for (int alpha = 2; alpha <= K; alpha += 2)
-      for (const pw::Term &t : pw::midpoint_terms(L, alpha)) {
-        if (t.l == 0) {
-          // the monopole carries no line-of-sight dependence: its alpha > 0 couplings vanish
-          if (t.c > 1e-12 || t.c < -1e-12) {
-            std::fprintf(stderr, "gen_contract: non-zero monopole coupling at alpha=%d\n", alpha);
-            return 1;
-          }
-          continue;
-        }
-        const int pg = mid_field_index(L, K, alpha, t.J2, t.mu2);
-        if (pg < 0) {
-          std::fprintf(stderr, "gen_contract: field (alpha=%d, J=%d, mu=%d) outside the field set\n",
-                       alpha, t.J2, t.mu2);
-          return 1;
-        }
-        by[{t.l, t.nu}][{pw::sh_index(t.J1, t.mu1), alpha / 2}].push_back({t.c, pg});
-      }
-    for (int l = 2; l <= L; l += 2)
-      for (int nu = -l; nu <= l; ++nu) {
-        std::fprintf(f, "    {\n      R t = (R)0;\n");
-        auto it = by.find({l, nu});
-        if (it != by.end())
-          for (auto &grp : it->second) {
-            std::fprintf(f, "      {\n        R u = (R)0;\n");
-            for (auto &cg : grp.second)
-              std::fprintf(f, "        u += (R)%.17g * g[%d];\n", cg.first, cg.second);
-            std::fprintf(f, "        t += (yD[%d] * Dp[%d]) * u;\n      }\n", grp.first.first,
-                         grp.first.second);
-          }
-        std::fprintf(f, "      A[%d] = t;\n    }\n", a_index(l, nu));
-      }
-    std::fprintf(f, "  }\n};\n");
-  }
-  const int all_shapes[][2] = {{2, 1}, {2, 2}, {2, 3}, {2, 4}, {4, 1}, {4, 2}, {4, 3}, {4, 4}};
-  for (const auto &shape : all_shapes) {
-    const int L = shape[0], K = shape[1];
-    const int NG = mid_all_nfields(L, K);
-    int NA = 0;
-    for (int l = 2; l <= L; l += 2) NA += 2 * l + 1;
-    std::fprintf(f, "template <typename R> struct MidReweightAll<%d, %d, R> {\n", L, K);
-    std::fprintf(f, "  static constexpr bool kGenerated = true;\n");
-    std::fprintf(f, "  static constexpr int NG = %d;\n  static constexpr int NA = %d;\n", NG, NA);
-    std::fprintf(f, "  __device__ __forceinline__ static void run(const R *g, const R *yD, const R *Dp, R *A) {\n");
-    std::map<std::pair<int, int>, std::map<std::pair<int, int>, std::vector<std::pair<double, int>>>> by;
-    for (int alpha = 1; alpha <= K; ++alpha)
-      for (const pw::Term &t : pw::midpoint_terms_all(L, alpha)) {
-        if (t.l == 0) {
-          if (t.c > 1e-12 || t.c < -1e-12) {
-            std::fprintf(stderr, "gen_contract: non-zero all-parity monopole coupling at alpha=%d\n", alpha);
-            return 1;
-          }
-          continue;
-        }
-        const int pg = mid_all_field_index(L, K, alpha, t.J2, t.mu2);
-        if (pg < 0) {
-          std::fprintf(stderr, "gen_contract: all-parity field (alpha=%d, J=%d, mu=%d) outside the field set\n",
-                       alpha, t.J2, t.mu2);
-          return 1;
-        }
-        by[{t.l, t.nu}][{pw::sh_index(t.J1, t.mu1), alpha}].push_back({t.c, pg});
-      }
-    for (int l = 2; l <= L; l += 2)
-      for (int nu = -l; nu <= l; ++nu) {
-        std::fprintf(f, "    {\n      R t = (R)0;\n");
-        auto it = by.find({l, nu});
-        if (it != by.end())
-          for (auto &grp : it->second) {
-            std::fprintf(f, "      {\n        R u = (R)0;\n");
-            for (auto &cg : grp.second)
-              std::fprintf(f, "        u += (R)%.17g * g[%d];\n", cg.first, cg.second);
-            std::fprintf(f, "        t += (yD[%d] * Dp[%d]) * u;\n      }\n", grp.first.first,
-                         grp.first.second);
-          }
-        std::fprintf(f, "      A[%d] = t;\n    }\n", a_index(l, nu));
-      }
-    std::fprintf(f, "  }\n};\n");
-  }
+  std::fprintf(f, "struct MidShape { int L, K, all, NG; };\nconstexpr MidShape kMidShapes[] = {\n");
+  for (const auto &sh : mid_shapes)
+    std::fprintf(f, "  {%d, %d, %d, %d},\n", sh.L, sh.K, sh.all ? 1 : 0, (int)mid_fields(sh.L, sh.K, sh.all).size());
+  std::fprintf(f, "};\n");
+  std::fclose(f);
+  f = std::fopen(argv[2], "w");
+  if (!f) return 1;
+  std::fprintf(f, "// Generated by gen_contract.cpp at build time; do not edit.\n");
+  std::fprintf(f, "#define PW_MIX_SHAPES(X)");
+  for (const auto &sh : mid_shapes) std::fprintf(f, " X(%d, %d, %s)", sh.L, sh.K, sh.all ? "true" : "false");
+  std::fprintf(f, "\n");
+  for (const auto &sh : mid_shapes)
+    if (!emit_mid(f, sh.L, sh.K, sh.all)) return 1;
   std::fclose(f);
   return 0;
 }

@@ -3,7 +3,6 @@
 //   contract_bis_reg  bisector P_l contraction with every field value of a mode in VGPRs
 //                     (Section 5.2 boxed estimator, real-harmonic basis)
 //   targets           bisector xi_l per-mode targets T_{l nu} (Section 6 boxed estimator)
-//   reweight          midpoint A_{l nu}(D) = sum Phi' y(D^) |D|^alpha g (Section 3.3, Appendix D)
 #include "kernels.h"
 
 #include "dev_core.h"
@@ -17,12 +16,6 @@ void upload_sh_const_generated(const ShConst &c) {
 }
 
 template <int L, int B, typename R> struct BisContract {
-  static constexpr bool kGenerated = false;
-};
-template <int L, int K, typename R> struct MidReweight {
-  static constexpr bool kGenerated = false;
-};
-template <int L, int K, typename R> struct MidReweightAll {
   static constexpr bool kGenerated = false;
 };
 #include "contract_gen.inc"
@@ -174,12 +167,8 @@ bool bis_contract_generated(int lmax, int bmax) {
 }
 
 int mid_reweight_nfields(int lmax, int order, int all_parity) {
-#define PW_MN(L, K) if (!all_parity && lmax == L && order == K) return MidReweight<L, K, float>::kGenerated ? MidReweight<L, K, float>::NG : -1;
-  PW_MN(2, 2) PW_MN(2, 4) PW_MN(2, 6) PW_MN(4, 2) PW_MN(4, 4) PW_MN(4, 6) PW_MN(6, 2) PW_MN(6, 4)
-#undef PW_MN
-#define PW_MNA(L, K) if (all_parity && lmax == L && order == K) return MidReweightAll<L, K, float>::kGenerated ? MidReweightAll<L, K, float>::NG : -1;
-  PW_MNA(2, 1) PW_MNA(2, 2) PW_MNA(2, 3) PW_MNA(2, 4) PW_MNA(4, 1) PW_MNA(4, 2) PW_MNA(4, 3) PW_MNA(4, 4)
-#undef PW_MNA
+  for (const MidShape &m : kMidShapes)
+    if (m.L == lmax && m.K == order && m.all == (all_parity ? 1 : 0)) return m.NG;
   return -1;
 }
 
@@ -245,75 +234,26 @@ void launch_targets(hipStream_t s, int prec, int N, int lmax, int bmax, const vo
 #undef PW_TG
 }
 
-// Midpoint real-space re-weighting: one thread per cell of the separation grid
-// (D = H * signed index, minimum image), g[i][cell] -> A[j][cell].  Parity-even (ALLP false):
-// even alpha and J1, Dp[i] = |D|^(2i); all-parity: every alpha and J1, Dp[i] = |D|^i.
-template <typename R, int L, int K, bool ALLP>
-__global__ void __launch_bounds__(256)
-k_reweight(const R *__restrict__ g, R *__restrict__ A, int N, R Hu) {
-  using MR = typename std::conditional<ALLP, MidReweightAll<L, K, R>, MidReweight<L, K, R>>::type;
-  constexpr int NSH = (K + 1) * (K + 1);
-  constexpr int NDP = ALLP ? K + 1 : K / 2 + 1;
-  const size_t ncell = (size_t)N * N * N;
-  // one cell per thread, no grid-stride loop: the fields' base addresses are then formed next
-  // to their loads instead of being kept live across a loop (up to 130 fields: more scalar
-  // registers than there are, spilled into vector lanes)
-  {
-    const size_t c = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= ncell) return;
-    const int x = (int)(c % N), y = (int)((c / N) % N), z = (int)(c / ((size_t)N * N));
-    const int sx = x < N / 2 ? x : x - N, sy = y < N / 2 ? y : y - N, sz = z < N / 2 ? z : z - N;
-    const R dx = (R)sx * Hu, dy = (R)sy * Hu, dz = (R)sz * Hu;  // D / unit
-    const R d2 = dx * dx + dy * dy + dz * dz;
-    R yD[NSH];
-#pragma unroll
-    for (int i = 0; i < NSH; ++i) yD[i] = 0;
-    R Dp[NDP];
-    Dp[0] = 1;
-    const R dstep = ALLP ? sqrt(d2) : d2;
-#pragma unroll
-    for (int i = 1; i < NDP; ++i) Dp[i] = Dp[i - 1] * dstep;
-    if (d2 > (R)0) {
-      const R ir = (R)1 / sqrt(d2);
-      real_sh_even<R, K, ALLP>(c_sh_gen, dx * ir, dy * ir, dz * ir, yD);
-    } else {
-      // D = 0: |D|^alpha = 0 for every alpha > 0, so the direction is immaterial
-      real_sh_even<R, K, ALLP>(c_sh_gen, (R)0, (R)0, (R)1, yD);
-    }
-    R gv[MR::NG];
-#pragma unroll
-    for (int i = 0; i < MR::NG; ++i) gv[i] = g[(size_t)i * ncell + c];
-    R av[MR::NA];
-    MR::run(gv, yD, Dp, av);
-#pragma unroll
-    for (int i = 0; i < MR::NA; ++i) A[(size_t)i * ncell + c] = av[i];
-  }
-}
+// ------------------------------------------------------------------------------ mix (by mesh size)
+#define PW_MIX_ARGS                                                                                \
+  hipStream_t s, int prec, int lmax, int order, int all_parity, const void *in, void *out, int rs, \
+      int nkx, int rso, double scale, double Hu, const void *tw
+void launch_mix_16(PW_MIX_ARGS);
+void launch_mix_32(PW_MIX_ARGS);
+void launch_mix_64(PW_MIX_ARGS);
+void launch_mix_128(PW_MIX_ARGS);
+void launch_mix_256(PW_MIX_ARGS);
+void launch_mix_512(PW_MIX_ARGS);
 
-template <typename R, int L, int K, bool ALLP>
-static void reweight_launch(hipStream_t s, int N, const void *g, void *A, double Hu) {
-  using MR = typename std::conditional<ALLP, MidReweightAll<L, K, R>, MidReweight<L, K, R>>::type;
-  if constexpr (MR::kGenerated) {
-    const size_t ncell = (size_t)N * N * N;
-    const unsigned blocks = (unsigned)((ncell + 255) / 256);  // at most 2^19 (N <= 512)
-    hipLaunchKernelGGL((k_reweight<R, L, K, ALLP>), dim3(blocks), dim3(256), 0, s, (const R *)g, (R *)A, N,
-                       (R)Hu);
+void launch_mix(hipStream_t s, int prec, int N, int lmax, int order, int all_parity, const void *in, void *out, int rs,
+                int nkx, int rso, double scale, double Hu, const void *tw) {
+  switch (N) {
+#define PW_MIX_CASE(n) \
+  case n: launch_mix_##n(s, prec, lmax, order, all_parity, in, out, rs, nkx, rso, scale, Hu, tw); break;
+    PW_MIX_CASE(16) PW_MIX_CASE(32) PW_MIX_CASE(64) PW_MIX_CASE(128) PW_MIX_CASE(256) PW_MIX_CASE(512)
+#undef PW_MIX_CASE
+    default: break;
   }
-}
-
-void launch_reweight(hipStream_t s, int prec, int N, int lmax, int order, int all_parity, const void *g, void *A,
-                     double Hu) {
-#define PW_RW(L, K, AP)                                                                           \
-  if (lmax == L && order == K && all_parity == AP) {                                              \
-    if (prec == 0) reweight_launch<float, L, K, AP>(s, N, g, A, Hu);                               \
-    else reweight_launch<double, L, K, AP>(s, N, g, A, Hu);                                        \
-    return;                                                                                       \
-  }
-  PW_RW(2, 2, 0) PW_RW(2, 4, 0) PW_RW(2, 6, 0) PW_RW(4, 2, 0) PW_RW(4, 4, 0) PW_RW(4, 6, 0) PW_RW(6, 2, 0)
-  PW_RW(6, 4, 0)
-  PW_RW(2, 1, 1) PW_RW(2, 2, 1) PW_RW(2, 3, 1) PW_RW(2, 4, 1) PW_RW(4, 1, 1) PW_RW(4, 2, 1) PW_RW(4, 3, 1)
-  PW_RW(4, 4, 1)
-#undef PW_RW
 }
 
 }  // namespace pw

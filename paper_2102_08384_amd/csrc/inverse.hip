@@ -4,10 +4,9 @@
 //                  output pruned to the retained z planes
 //   fziz           midpoint g fields: forward FFT along z, the product conj(D) Q / W^2
 //                  (Section 3.2) and the inverse FFT along z in one pass over each pencil
-//   ix             complex-to-real inverse FFT along x of field pairs; either stores the real
-//                  fields or, for xi_l, weights them by |D|^alpha y_J^mu(D^) times the per-field
-//                  multipole coefficient and bins the sums into r-shells in FP64
-//                  (Section 4.3 midpoint estimator, Section 6 bisector estimator)
+//   ix             xi_l: complex-to-real inverse FFT along x of field pairs, weighted by
+//                  |D|^alpha y_J^mu(D^) times the per-field multipole coefficient and binned into
+//                  r-shells in FP64 (Section 4.3 midpoint estimator, Section 6 bisector estimator)
 //   contract_mid   midpoint P_l contraction sum_nu y_l^nu(k^) Re[G + A] (Section 3.3 boxed
 //                  estimator in the real-harmonic basis) with FP64 shell sums
 //   finalize_xi    xi_l = (4 pi / I) sum / (N_a H^3)
@@ -328,16 +327,16 @@ void launch_fziz(hipStream_t s, int prec, int N, const void *in, void *prod, voi
 // ------------------------------------------------------------------------------ ix
 constexpr int kMaxEll = 5;  // multipoles 0, 2, .., 8
 
-template <typename R, int N, int MODE>
+template <typename R, int N>
 __global__ void __launch_bounds__(FxShape<N>::THREADS)
-k_ix(const cplx<R> *__restrict__ in, R *__restrict__ out, int rs, const FieldJob *__restrict__ jobs, int njobs,
+k_ix(const cplx<R> *__restrict__ in, int rs, const FieldJob *__restrict__ jobs, int njobs,
      const R *__restrict__ coef, int nell, int nz, int ny, const int *__restrict__ zidx,
      const int *__restrict__ yidx, R Hu, double Hd, R scale, const int *__restrict__ bin_of_s2, int64_t n_s2,
      int nbins, double *__restrict__ acc, const cplx<R> *__restrict__ tw) {
   constexpr int T = FxShape<N>::T, ROWS = FxShape<N>::ROWS, NKX = N / 2 + 1;
   constexpr int LN = N + N / 8;
   __shared__ cplx<R> lds[ROWS * LN];
-  extern __shared__ double bacc[];  // mode 1: (nell + 2) * nbins
+  extern __shared__ double bacc[];  // (nell + 2) * nbins
   const int rl = threadIdx.x / T, t = threadIdx.x % T;
   const int64_t nrows = (int64_t)nz * ny;
   const int64_t row = (int64_t)blockIdx.x * ROWS + rl;
@@ -349,30 +348,27 @@ k_ix(const cplx<R> *__restrict__ in, R *__restrict__ out, int rs, const FieldJob
   auto sync = []() { __syncthreads(); };
   const int sy = y < N / 2 ? y : y - N, sz = z < N / 2 ? z : z - N;
 
-
-  // mode 1 geometry of the eight cells this lane holds
+  // geometry of the eight cells this lane holds
   R ux[8], uy[8], uz[8], dm[8];
   int bin[8];
   R X[kMaxEll][8];
-  if constexpr (MODE == 1) {
-    const int nacc = (nell + 2) * nbins;
-    for (int i = threadIdx.x; i < nacc; i += blockDim.x) bacc[i] = 0.0;
+  const int nacc = (nell + 2) * nbins;
+  for (int i = threadIdx.x; i < nacc; i += blockDim.x) bacc[i] = 0.0;
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      const int x = t + s * T;
-      const int sx = x < N / 2 ? x : x - N;
-      const int64_t s2 = (int64_t)sx * sx + (int64_t)sy * sy + (int64_t)sz * sz;
-      bin[s] = (live && s2 < n_s2) ? bin_of_s2[s2] : -1;
-      dm[s] = Hu * sqrt((R)s2);  // |D| / unit
-      if (s2 > 0) {
-        const R ir = (R)1 / sqrt((R)s2);
-        ux[s] = (R)sx * ir; uy[s] = (R)sy * ir; uz[s] = (R)sz * ir;
-      } else {
-        ux[s] = 0; uy[s] = 0; uz[s] = 1;
-      }
-#pragma unroll
-      for (int l = 0; l < kMaxEll; ++l) X[l][s] = 0;
+  for (int s = 0; s < 8; ++s) {
+    const int x = t + s * T;
+    const int sx = x < N / 2 ? x : x - N;
+    const int64_t s2 = (int64_t)sx * sx + (int64_t)sy * sy + (int64_t)sz * sz;
+    bin[s] = (live && s2 < n_s2) ? bin_of_s2[s2] : -1;
+    dm[s] = Hu * sqrt((R)s2);  // |D| / unit
+    if (s2 > 0) {
+      const R ir = (R)1 / sqrt((R)s2);
+      ux[s] = (R)sx * ir; uy[s] = (R)sy * ir; uz[s] = (R)sz * ir;
+    } else {
+      ux[s] = 0; uy[s] = 0; uz[s] = 1;
     }
+#pragma unroll
+    for (int l = 0; l < kMaxEll; ++l) X[l][s] = 0;
   }
   ShRec8<R> rec;
   rec.init();
@@ -399,114 +395,91 @@ k_ix(const cplx<R> *__restrict__ in, R *__restrict__ out, int rs, const FieldJob
     for (int s = 0; s < 8; ++s) v[s] = at(t + s * T);
     sync();
     fft_pencil<R, N, true>(v, t, tw, at, sync);
-    if constexpr (MODE == 0) {
-      if (live) {
-        R *oa = out + (size_t)J.pa * N * N * N + ((size_t)z * N + y) * N;
-        R *ob = out + (size_t)(J.pb < 0 ? 0 : J.pb) * N * N * N + ((size_t)z * N + y) * N;
+    R ya[8], yb[8];
+    if (J.kind == 0) {
+      rec.set_m(J.m, ux, uy);
+      rec.advance(c_sh_inv, J.Ja, uz);
+      const R n = sh_n<R>(c_sh_inv, J.Ja, J.m);
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
-          oa[t + s * T] = v[s].x * scale;
-          if (J.pb >= 0) ob[t + s * T] = v[s].y * scale;
-        }
+      for (int s = 0; s < 8; ++s) {
+        R w = n * rec.q0[s];
+        for (int a = 0; a < J.alpha; ++a) w *= dm[s];
+        ya[s] = w * rec.cr[s];
+        yb[s] = w * rec.ci[s];
       }
     } else {
-      R ya[8], yb[8];
-      if (J.kind == 0) {
-        rec.set_m(J.m, ux, uy);
-        rec.advance(c_sh_inv, J.Ja, uz);
-        const R n = sh_n<R>(c_sh_inv, J.Ja, J.m);
+      rec.set_m(0, ux, uy);
+      rec.advance(c_sh_inv, J.Ja, uz);
+      const R na = sh_n<R>(c_sh_inv, J.Ja, 0);
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
-          R w = n * rec.q0[s];
-          for (int a = 0; a < J.alpha; ++a) w *= dm[s];
-          ya[s] = w * rec.cr[s];
-          yb[s] = w * rec.ci[s];
-        }
-      } else {
-        rec.set_m(0, ux, uy);
-        rec.advance(c_sh_inv, J.Ja, uz);
-        const R na = sh_n<R>(c_sh_inv, J.Ja, 0);
-#pragma unroll
-        for (int s = 0; s < 8; ++s) {
-          R w = na * rec.q0[s];
-          for (int a = 0; a < J.alpha; ++a) w *= dm[s];
-          ya[s] = w;
-          yb[s] = 0;
-        }
-        if (J.Jb >= 0) {
-          rec.advance(c_sh_inv, J.Jb, uz);
-          const R nb = sh_n<R>(c_sh_inv, J.Jb, 0);
-#pragma unroll
-          for (int s = 0; s < 8; ++s) {
-            R w = nb * rec.q0[s];
-            for (int a = 0; a < J.alpha_b; ++a) w *= dm[s];
-            yb[s] = w;
-          }
-        }
+      for (int s = 0; s < 8; ++s) {
+        R w = na * rec.q0[s];
+        for (int a = 0; a < J.alpha; ++a) w *= dm[s];
+        ya[s] = w;
+        yb[s] = 0;
       }
-      const R *ca = coef + (size_t)jb * 2 * nell, *cb = ca + nell;
+      if (J.Jb >= 0) {
+        rec.advance(c_sh_inv, J.Jb, uz);
+        const R nb = sh_n<R>(c_sh_inv, J.Jb, 0);
 #pragma unroll
-      for (int l = 0; l < kMaxEll; ++l) {
-        if (l < nell) {
-          const R fa = ca[l], fb = cb[l];
-#pragma unroll
-          for (int s = 0; s < 8; ++s) X[l][s] += fa * ya[s] * v[s].x + fb * yb[s] * v[s].y;
+        for (int s = 0; s < 8; ++s) {
+          R w = nb * rec.q0[s];
+          for (int a = 0; a < J.alpha_b; ++a) w *= dm[s];
+          yb[s] = w;
         }
       }
     }
-  }
-  if constexpr (MODE == 1) {
-    sync();  // bacc cleared by every thread before any accumulation
+    const R *ca = coef + (size_t)jb * 2 * nell, *cb = ca + nell;
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      const int b = bin[s];
-      if (b < 0) continue;
-      const int x = t + s * T;
-      const int sx = x < N / 2 ? x : x - N;
-      const double s2 = (double)sx * sx + (double)sy * sy + (double)sz * sz;
+    for (int l = 0; l < kMaxEll; ++l) {
+      if (l < nell) {
+        const R fa = ca[l], fb = cb[l];
 #pragma unroll
-      for (int l = 0; l < kMaxEll; ++l)
-        if (l < nell) atomicAdd(&bacc[l * nbins + b], (double)(X[l][s] * scale));
-      atomicAdd(&bacc[nell * nbins + b], 1.0);
-      atomicAdd(&bacc[(nell + 1) * nbins + b], Hd * sqrt(s2));
+        for (int s = 0; s < 8; ++s) X[l][s] += fa * ya[s] * v[s].x + fb * yb[s] * v[s].y;
+      }
     }
-    sync();
-    const int nacc = (nell + 2) * nbins;
-    for (int i = threadIdx.x; i < nacc; i += blockDim.x)
-      if (bacc[i] != 0.0) atomicAdd(&acc[i], bacc[i]);
   }
+  sync();  // bacc cleared by every thread before any accumulation
+#pragma unroll
+  for (int s = 0; s < 8; ++s) {
+    const int b = bin[s];
+    if (b < 0) continue;
+    const int x = t + s * T;
+    const int sx = x < N / 2 ? x : x - N;
+    const double s2 = (double)sx * sx + (double)sy * sy + (double)sz * sz;
+#pragma unroll
+    for (int l = 0; l < kMaxEll; ++l)
+      if (l < nell) atomicAdd(&bacc[l * nbins + b], (double)(X[l][s] * scale));
+    atomicAdd(&bacc[nell * nbins + b], 1.0);
+    atomicAdd(&bacc[(nell + 1) * nbins + b], Hd * sqrt(s2));
+  }
+  sync();
+  for (int i = threadIdx.x; i < nacc; i += blockDim.x)
+    if (bacc[i] != 0.0) atomicAdd(&acc[i], bacc[i]);
 }
 
 template <typename R, int N>
-static void ix_launch(hipStream_t s, int mode, const void *in, void *out, int rs, const FieldJob *jobs, int njobs,
-                      const void *coef, int nell, int nz, int ny, const int *zidx, const int *yidx, double H,
-                      double unit, double scale, const int *bin_of_s2, int64_t n_s2, int nbins, double *acc,
-                      const void *tw) {
+static void ix_launch(hipStream_t s, const void *in, int rs, const FieldJob *jobs, int njobs, const void *coef,
+                      int nell, int nz, int ny, const int *zidx, const int *yidx, double H, double unit, double scale,
+                      const int *bin_of_s2, int64_t n_s2, int nbins, double *acc, const void *tw) {
   constexpr int ROWS = FxShape<N>::ROWS;
   const int64_t nrows = (int64_t)nz * ny;
   dim3 grid((unsigned)((nrows + ROWS - 1) / ROWS));
-  if (mode == 0) {
-    hipLaunchKernelGGL((k_ix<R, N, 0>), grid, dim3(FxShape<N>::THREADS), 0, s, (const cplx<R> *)in, (R *)out,
-                       rs, jobs, njobs, (const R *)coef, nell, nz, ny, zidx, yidx, (R)(H / unit), H, (R)scale, bin_of_s2,
-                       n_s2, nbins, acc, (const cplx<R> *)tw);
-  } else {
-    size_t sh = (size_t)(nell + 2) * nbins * sizeof(double);
-    hipLaunchKernelGGL((k_ix<R, N, 1>), grid, dim3(FxShape<N>::THREADS), sh, s, (const cplx<R> *)in, (R *)out,
-                       rs, jobs, njobs, (const R *)coef, nell, nz, ny, zidx, yidx, (R)(H / unit), H, (R)scale, bin_of_s2,
-                       n_s2, nbins, acc, (const cplx<R> *)tw);
-  }
+  const size_t sh = (size_t)(nell + 2) * nbins * sizeof(double);
+  hipLaunchKernelGGL((k_ix<R, N>), grid, dim3(FxShape<N>::THREADS), sh, s, (const cplx<R> *)in, rs, jobs, njobs,
+                     (const R *)coef, nell, nz, ny, zidx, yidx, (R)(H / unit), H, (R)scale, bin_of_s2, n_s2, nbins, acc,
+                     (const cplx<R> *)tw);
 }
 
-void launch_ix(hipStream_t s, int prec, int N, int mode, const void *in, void *out, int rs, const FieldJob *jobs,
-               int njobs, const void *coef, int nell, int nz, int ny, const int *zidx, const int *yidx, double H,
-               double unit, double scale, const int *bin_of_s2, int64_t n_s2, int nbins, double *acc,
-               const void *tw) {
+void launch_ix(hipStream_t s, int prec, int N, const void *in, int rs, const FieldJob *jobs, int njobs,
+               const void *coef, int nell, int nz, int ny, const int *zidx, const int *yidx, double H, double unit,
+               double scale, const int *bin_of_s2, int64_t n_s2, int nbins, double *acc, const void *tw) {
   if (njobs <= 0 || nz <= 0 || ny <= 0 || nell > kMaxEll) return;
   if (prec == 0) {
-    PW_DISPATCH_N(ix_launch, float, s, mode, in, out, rs, jobs, njobs, coef, nell, nz, ny, zidx, yidx, H, unit, scale,
+    PW_DISPATCH_N(ix_launch, float, s, in, rs, jobs, njobs, coef, nell, nz, ny, zidx, yidx, H, unit, scale,
                   bin_of_s2, n_s2, nbins, acc, tw)
   } else {
-    PW_DISPATCH_N(ix_launch, double, s, mode, in, out, rs, jobs, njobs, coef, nell, nz, ny, zidx, yidx, H, unit, scale,
+    PW_DISPATCH_N(ix_launch, double, s, in, rs, jobs, njobs, coef, nell, nz, ny, zidx, yidx, H, unit, scale,
                   bin_of_s2, n_s2, nbins, acc, tw)
   }
 }

@@ -31,7 +31,6 @@ struct DevNorm {
 // kind 0: fields (J, +m) and (J, -m), m > 0, of weight (2r)^-alpha;  pa / pb their indices.
 // kind 1: fields (Ja, 0) of weight (2r)^-alpha and (Jb, 0) of weight (2r)^-alpha_b
 //         (Jb < 0: single field, pb < 0).
-// kind 2: no weighting: real input fields Ja and Jb (Jb < 0: none) of a field stack.
 // Jobs must be sorted by m, then by J (the x pass carries its recurrences across jobs).
 // The inverse x pass reads the same records with |D|^alpha y(D^) in place of (2r)^-alpha y(x^).
 struct FieldJob {
@@ -143,10 +142,9 @@ inline int row_stride(int nkx, int prec) {
 // product (2r)^-alpha |D|^alpha is unchanged while fields of every alpha stay O(1)).
 // rowlist (may be null: every row) restricts the pass to the non-empty rows; the output rows of
 // empty ones are not written (the y pass reads them as zeros).
-// kind FX_PLAIN: every job is kind 2 (pairs of real input fields, no weighting); else kinds 0 and 1.
 // x-pass inputs: FX_HARMONIC generates y_J^mu(x^) F (bisector), FX_RADIAL also (u/2r)^alpha
-// (midpoint), FX_PLAIN transforms real input fields of a stack (midpoint A fields)
-enum { FX_HARMONIC = 0, FX_RADIAL = 1, FX_PLAIN = 2 };
+// (midpoint)
+enum { FX_HARMONIC = 0, FX_RADIAL = 1 };
 void launch_fx(hipStream_t s, int prec, int N, int kind, const void *mesh, void *out, const FieldJob *jobs,
                int njobs, int nkx, int rs, const double *b0, double H, double unit, const void *tw,
                const int *rowlist, const DevNorm *norm, const Batch *batch = nullptr,
@@ -228,17 +226,19 @@ void launch_fziz(hipStream_t s, int prec, int N, const void *in, void *prod, voi
                  const int *planemask, ColTune tune = ColTune());
 // Inverse x pass (complex-to-real) of pair jobs on the rows (zr, yr) of in[p][zr][yr * rs + kx],
 // kx <= N/2, scaled by `scale`.
-//   mode 0: out[p][z][y][x] real fields (nz = ny = N).
-//   mode 1: X_l += coef[j][side][l] (|D| / unit)^alpha y_J^mu(D^) h, then FP64 r-binning of
-//           X_l into acc[l][b], acc[nell][b] (count), acc[nell + 1][b] (sum |D|).
-void launch_ix(hipStream_t s, int prec, int N, int mode, const void *in, void *out, int rs,
+//   X_l += coef[j][side][l] (|D| / unit)^alpha y_J^mu(D^) h, then FP64 r-binning of
+//   X_l into acc[l][b], acc[nell][b] (count), acc[nell + 1][b] (sum |D|).
+void launch_ix(hipStream_t s, int prec, int N, const void *in, int rs,
                const FieldJob *jobs, int njobs, const void *coef, int nell, int nz, int ny,
                const int *zidx, const int *yidx, double H, double unit, double scale, const int *bin_of_s2,
                int64_t n_s2, int nbins, double *acc, const void *tw);
-// Midpoint real-space re-weighting: A_{l nu}(D) from the alpha > 0 g fields (generated),
-// with |D| in the length unit of the forward weights (Hu = H / unit).
-void launch_reweight(hipStream_t s, int prec, int N, int lmax, int order, int all_parity, const void *g, void *A,
-                     double Hu);
+// Midpoint P real-space step (mix.hip): the y-pass output of the g fields in[p][z][y * rs + kx],
+// kx <= N/2, through the inverse x pass (scaled by `scale`), the generated re-weighting
+// A_{l nu}(D) with |D| in the length unit of the forward weights (Hu = H / unit), and the forward x
+// pass of the A fields, out[i][z][y * rso + kx], kx < nkx.  prec, N and (lmax, order, all_parity)
+// select a built shape (mid_reweight_generated).
+void launch_mix(hipStream_t s, int prec, int N, int lmax, int order, int all_parity, const void *in, void *out, int rs,
+                int nkx, int rso, double scale, double Hu, const void *tw);
 // Bisector xi targets: T[t][i] = sum S Re(conj(R_p1) R_p2) / W(k)^2 over the full
 // pencil-major spectra (i = q * N + kz, q = ky * rs + kx), written as real values (generated).
 // Field p of spec starts at p * mstride; target t of T at t * nmodes.

@@ -103,36 +103,9 @@ struct ShPair8 {
   }
 };
 
-// LDS ordering between the lanes of one wavefront (LDS executes a wavefront's instructions in
-// order; this keeps the compiler from moving accesses across the exchange point).
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// value of lane `src` (0..63) of this wavefront
-template <typename R>
-__device__ __forceinline__ cplx<R> lane_fetch(int src, cplx<R> v) {
-  const int addr = src << 2;
-  if constexpr (sizeof(R) == 4) {
-    return mk<R>(__int_as_float(__builtin_amdgcn_ds_bpermute(addr, __float_as_int(v.x))),
-                 __int_as_float(__builtin_amdgcn_ds_bpermute(addr, __float_as_int(v.y))));
-  } else {
-    const long long xb = __double_as_longlong(v.x), yb = __double_as_longlong(v.y);
-    const int xl = __builtin_amdgcn_ds_bpermute(addr, (int)(xb & 0xffffffffLL));
-    const int xh = __builtin_amdgcn_ds_bpermute(addr, (int)(xb >> 32));
-    const int yl = __builtin_amdgcn_ds_bpermute(addr, (int)(yb & 0xffffffffLL));
-    const int yh = __builtin_amdgcn_ds_bpermute(addr, (int)(yb >> 32));
-    return mk<R>(__longlong_as_double(((long long)xh << 32) | (unsigned)xl),
-                 __longlong_as_double(((long long)yh << 32) | (unsigned)yl));
-  }
-}
-
 // One block = ROWS rows (z, y) of N cells; lane t of a row holds cells x = t + s*T.  For every
-// job, two real fields (F (u/2r)^alpha y_J^mu, or two plain input fields when PLAIN) go through
-// one complex FFT Z = FFT(a + i b) and are separated as A(k) = (Z(k) + conj Z(N-k)) / 2,
-// B(k) = (Z(k) - conj Z(N-k)) / 2i for kx < nkx.  When a row is one wavefront (T = 64) the FFT's
+// job, two real fields (F (u/2r)^alpha y_J^mu) go through one complex FFT Z = FFT(a + i b) and are
+// separated as A(k) = (Z(k) + conj Z(N-k)) / 2, B(k) = (Z(k) - conj Z(N-k)) / 2i for kx < nkx.  When a row is one wavefront (T = 64) the FFT's
 // exchanges need only wavefront ordering and Z(N-k) comes from the partner lane by a cross-lane
 // permute; otherwise the rows of the block share barriers and the separation reads LDS.
 // FP32 at N = 512 fits three wavefronts per SIMD without spills (FP64 would spill).
@@ -140,7 +113,7 @@ __device__ __forceinline__ cplx<R> lane_fetch(int src, cplx<R> v) {
 // 1/r; otherwise (bisector fields) it keeps z/r, the only radial quantity the harmonics need,
 // and 1/r is recomputed when the recurrence changes m.  Both fields of a job enter the
 // transform scaled by 1/2 (exactly), which is the factor of the two-real-field separation.
-template <typename R, int N, bool PLAIN, bool RADIAL, int ROWS = FxShape<N>::ROWS>
+template <typename R, int N, bool RADIAL, int ROWS = FxShape<N>::ROWS>
 __global__ void __launch_bounds__(ROWS * FxShape<N>::T)
 __attribute__((amdgpu_waves_per_eu((sizeof(R) == 4 && N == 512) ? 3 : 1, 8)))
 k_fx(const R *__restrict__ mesh, cplx<R> *__restrict__ out, const FieldJob *__restrict__ jobs,
@@ -186,112 +159,101 @@ k_fx(const R *__restrict__ mesh, cplx<R> *__restrict__ out, const FieldJob *__re
     const R r = sqrt(px * px + py * py + pz * pz);
     return (r > (R)0) ? (R)1 / r : (R)0;
   };
-  if constexpr (!PLAIN) {
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      f[s] = live ? mesh[(size_t)row * N + t + s * T] : (R)0;
-      const R ir = inv_r(s);
-      g[s] = RADIAL ? ir : (ir > (R)0 ? pz * ir : (R)1);
-    }
+  for (int s = 0; s < 8; ++s) {
+    f[s] = live ? mesh[(size_t)row * N + t + s * T] : (R)0;
+    const R ir = inv_r(s);
+    g[s] = RADIAL ? ir : (ir > (R)0 ? pz * ir : (R)1);
   }
   const size_t fstride = (size_t)N * N * rs;  // rows padded to rs (128-byte aligned)
   ShPair8<R> rec;
-  if constexpr (!PLAIN) rec.init();
+  rec.init();
   for (int jb = 0; jb < njobs; ++jb) {
     const FieldJob J = jobs[jb];
     cplx<R> v[8];
-    if constexpr (PLAIN) {
-      // two real input fields of the stack at `mesh` (the second may be absent)
-      const R *fa = mesh + (size_t)J.Ja * N * N * N + (size_t)row * N;
-      const R *fb = mesh + (size_t)(J.Jb < 0 ? 0 : J.Jb) * N * N * N + (size_t)row * N;
+    // kind 0: (J, +m) and (J, -m) at one alpha: norm Q_J^m {Re, Im}(x + iy)^m;
+    // kind 1: (Ja, 0) and (Jb, 0) (Jb < 0: none), each at its own alpha.
+    // Written as one branch-free form: the second field uses ci + 1 = 1 when m = 0.
+    const bool k0 = (J.kind == 0);
+    const int Jb = (k0 || J.Jb < 0) ? J.Ja : J.Jb;
+    const R na = (R)0.5 * sh_n<R>(c_sh, J.Ja, J.m);
+    const R nb = k0 ? na : (J.Jb >= 0 ? (R)0.5 * sh_n<R>(c_sh, Jb, 0) : (R)0);
+    const R dci = k0 ? (R)0 : (R)1;
+    R wa[8];
 #pragma unroll
-      for (int s = 0; s < 8; ++s)
-        v[s] = mk<R>((R)0.5 * fa[t + s * T], J.Jb >= 0 ? (R)0.5 * fb[t + s * T] : (R)0);
-    } else {
-      // kind 0: (J, +m) and (J, -m) at one alpha: norm Q_J^m {Re, Im}(x + iy)^m;
-      // kind 1: (Ja, 0) and (Jb, 0) (Jb < 0: none), each at its own alpha.
-      // Written as one branch-free form: the second field uses ci + 1 = 1 when m = 0.
-      const bool k0 = (J.kind == 0);
-      const int Jb = (k0 || J.Jb < 0) ? J.Ja : J.Jb;
-      const R na = (R)0.5 * sh_n<R>(c_sh, J.Ja, J.m);
-      const R nb = k0 ? na : (J.Jb >= 0 ? (R)0.5 * sh_n<R>(c_sh, Jb, 0) : (R)0);
-      const R dci = k0 ? (R)0 : (R)1;
-      R wa[8];
+    for (int s = 0; s < 8; ++s) wa[s] = f[s] * na;
+    if constexpr (RADIAL) {
+      for (int a = 0; a < J.alpha; ++a) {
 #pragma unroll
-      for (int s = 0; s < 8; ++s) wa[s] = f[s] * na;
-      if constexpr (RADIAL) {
-        for (int a = 0; a < J.alpha; ++a) {
-#pragma unroll
-          for (int s = 0; s < 8; ++s) wa[s] *= uhalf * g[s];  // u / (2r): lengths in the unit u
-        }
+        for (int s = 0; s < 8; ++s) wa[s] *= uhalf * g[s];  // u / (2r): lengths in the unit u
       }
-      if (J.m != rec.m_cur) {
-        R ux[8], uy[8];
+    }
+    if (J.m != rec.m_cur) {
+      R ux[8], uy[8];
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
-          const R ir = RADIAL ? g[s] : inv_r(s);
-          ux[s] = (b0x + (R)(t + s * T) * H) * ir;
-          uy[s] = py * ir;
-        }
-        rec.set_m(J.m, ux, uy);
+      for (int s = 0; s < 8; ++s) {
+        const R ir = RADIAL ? g[s] : inv_r(s);
+        ux[s] = (b0x + (R)(t + s * T) * H) * ir;
+        uy[s] = py * ir;
       }
-      if constexpr (!RADIAL) {
-        rec.advance_uz(c_sh, J.Ja, g);
-        if (k0) {
-          // (J, +m) and (J, -m): one Legendre factor, the real and imaginary parts of (x + iy)^m
-          rec.with_cur([&](const R *q) {
-#pragma unroll
-            for (int s = 0; s < 8; ++s) {
-              const R tq = wa[s] * q[s];
-              v[s].x = tq * rec.cr[s];
-              v[s].y = tq * rec.ci[s];
-            }
-          });
-        } else {
-          // (Ja, 0) and (Jb, 0): m = 0, so (x + iy)^0 = 1
-          rec.with_cur([&](const R *q) {
-#pragma unroll
-            for (int s = 0; s < 8; ++s) v[s].x = wa[s] * q[s];
-          });
-          if (J.Jb >= 0) {
-            rec.advance_uz(c_sh, J.Jb, g);
-            rec.with_cur([&](const R *q) {
-#pragma unroll
-              for (int s = 0; s < 8; ++s) v[s].y = f[s] * nb * q[s];
-            });
-          } else {
-#pragma unroll
-            for (int s = 0; s < 8; ++s) v[s].y = (R)0;
-          }
-        }
-      } else {
-        rec.advance(c_sh, J.Ja, pz, g);
+      rec.set_m(J.m, ux, uy);
+    }
+    if constexpr (!RADIAL) {
+      rec.advance_uz(c_sh, J.Ja, g);
+      if (k0) {
+        // (J, +m) and (J, -m): one Legendre factor, the real and imaginary parts of (x + iy)^m
         rec.with_cur([&](const R *q) {
 #pragma unroll
-          for (int s = 0; s < 8; ++s) v[s].x = wa[s] * q[s] * rec.cr[s];
+          for (int s = 0; s < 8; ++s) {
+            const R tq = wa[s] * q[s];
+            v[s].x = tq * rec.cr[s];
+            v[s].y = tq * rec.ci[s];
+          }
         });
-        rec.advance(c_sh, Jb, pz, g);
-        if (J.alpha_b == J.alpha) {
-          const R rb = nb / na;  // na > 0 always
+      } else {
+        // (Ja, 0) and (Jb, 0): m = 0, so (x + iy)^0 = 1
+        rec.with_cur([&](const R *q) {
+#pragma unroll
+          for (int s = 0; s < 8; ++s) v[s].x = wa[s] * q[s];
+        });
+        if (J.Jb >= 0) {
+          rec.advance_uz(c_sh, J.Jb, g);
           rec.with_cur([&](const R *q) {
 #pragma unroll
-            for (int s = 0; s < 8; ++s) v[s].y = wa[s] * rb * q[s] * (rec.ci[s] + dci);
+            for (int s = 0; s < 8; ++s) v[s].y = f[s] * nb * q[s];
           });
         } else {
-          R wb[8];
 #pragma unroll
-          for (int s = 0; s < 8; ++s) wb[s] = f[s] * nb;
-          if constexpr (RADIAL) {
-            for (int a = 0; a < J.alpha_b; ++a) {
-#pragma unroll
-              for (int s = 0; s < 8; ++s) wb[s] *= uhalf * g[s];
-            }
-          }
-          rec.with_cur([&](const R *q) {
-#pragma unroll
-            for (int s = 0; s < 8; ++s) v[s].y = wb[s] * q[s] * (rec.ci[s] + dci);
-          });
+          for (int s = 0; s < 8; ++s) v[s].y = (R)0;
         }
+      }
+    } else {
+      rec.advance(c_sh, J.Ja, pz, g);
+      rec.with_cur([&](const R *q) {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) v[s].x = wa[s] * q[s] * rec.cr[s];
+      });
+      rec.advance(c_sh, Jb, pz, g);
+      if (J.alpha_b == J.alpha) {
+        const R rb = nb / na;  // na > 0 always
+        rec.with_cur([&](const R *q) {
+#pragma unroll
+          for (int s = 0; s < 8; ++s) v[s].y = wa[s] * rb * q[s] * (rec.ci[s] + dci);
+        });
+      } else {
+        R wb[8];
+#pragma unroll
+        for (int s = 0; s < 8; ++s) wb[s] = f[s] * nb;
+        if constexpr (RADIAL) {
+          for (int a = 0; a < J.alpha_b; ++a) {
+#pragma unroll
+            for (int s = 0; s < 8; ++s) wb[s] *= uhalf * g[s];
+          }
+        }
+        rec.with_cur([&](const R *q) {
+#pragma unroll
+          for (int s = 0; s < 8; ++s) v[s].y = wb[s] * q[s] * (rec.ci[s] + dci);
+        });
       }
     }
     fft_pencil<R, N, false>(v, t, tw, at, sync);
@@ -351,15 +313,14 @@ static void fx_launch(hipStream_t s, int kind, const void *mesh, void *out, cons
   ba.n = 0;
   if (batch) ba = *batch;
   const unsigned nb = ba.n ? ba.n : 1;
-#define PW_FX(PL, RAD, RW)                                                                                       \
-  hipLaunchKernelGGL((k_fx<R, N, PL, RAD, RW>), dim3((unsigned)((size_t)N * N / (RW)), 1, nb),                  \
+#define PW_FX(RAD, RW)                                                                                           \
+  hipLaunchKernelGGL((k_fx<R, N, RAD, RW>), dim3((unsigned)((size_t)N * N / (RW)), 1, nb),                  \
                      dim3((RW) * FxShape<N>::T), 0, s, (const R *)mesh, (cplx<R> *)out, jobs, njobs, nkx, rs,    \
                      (R)b0[0], (R)b0[1], (R)b0[2], (R)H, (R)(0.5 * unit), (const cplx<R> *)tw, rowlist, norm, ba)
 #define PW_FX_KIND(RW)                                                                                           \
   do {                                                                                                           \
-    if (kind == FX_PLAIN) PW_FX(true, false, RW);                                                                \
-    else if (kind == FX_RADIAL) PW_FX(false, true, RW);                                                          \
-    else PW_FX(false, false, RW);                                                                                \
+    if (kind == FX_RADIAL) PW_FX(true, RW);                                                                      \
+    else PW_FX(false, RW);                                                                                       \
   } while (0)
   // other row counts per workgroup where a row is one wavefront (FP32 at N = 512)
   if constexpr (sizeof(R) == 4 && FxShape<N>::T == 64) {

@@ -434,9 +434,6 @@ HostPlan build_host_plan(const pw_config &c) {
       if (mid_reweight_nfields(c.ell_max, c.order, h.all_parity) != h.n_inv)
         plan_fail(PW_EINVAL, "internal: midpoint field set differs from the re-weighting kernel's");
       for (int l = 2; l <= c.ell_max; l += 2) h.n_a += 2 * l + 1;
-      for (int i = 0; i < h.n_a; i += 2)
-        h.ajobs.push_back(FieldJob{0, 2, i, 0, (i + 1 < h.n_a) ? i + 1 : -1, i,
-                                   (i + 1 < h.n_a) ? i + 1 : -1, 0});
     }
   }
 
@@ -457,15 +454,13 @@ HostPlan build_host_plan(const pw_config &c) {
       h.t_ell.push_back(kv.first.first / 2);
     }
   }
-  const size_t rsz = h.prec == PW_FP32 ? 4 : 8, csz = 2 * rsz;
+  const size_t csz = h.prec == PW_FP32 ? 8 : 16;
   if (h.path == PATH_MID_PK && h.n_a > 0) {
     // buffer A: the alpha = 0 products, then a region (avail) that holds in turn the retained z
-    // planes, the real g fields and the A fields' x-pass and z-pass outputs; B holds the y-pass
-    // outputs and the re-weighted A fields in real space
+    // planes and the A fields' x-pass and z-pass outputs; B holds the y-pass outputs
     const size_t sfull = (size_t)N * h.fwd.npen * csz, sb = spectrum_buffer_bytes(h);
     const size_t front = (size_t)h.n_inplace * sfull, avail = sb > front ? sb - front : 0;
-    if ((size_t)h.n_inv * h.nz * h.fwd.npen * csz > avail || (size_t)h.n_inv * N * N * N * rsz > avail ||
-        (size_t)h.n_a * N * N * N * rsz > sb || (size_t)h.n_a * N * N * h.sph.rs * csz > avail ||
+    if ((size_t)h.n_inv * h.nz * h.fwd.npen * csz > avail || (size_t)h.n_a * N * N * h.sph.rs * csz > avail ||
         (size_t)h.n_a * h.sph.mstride * csz > avail)
       plan_fail(PW_EINVAL, "internal: A fields do not fit the spectrum buffer");
   }

@@ -96,9 +96,7 @@ struct HostPlan {
   std::vector<FieldJob> ijobs;   // pair jobs of the inverse x pass (indices into the stack)
   std::vector<double> icoef;     // xi: [ijob][2][nell] per-field multipole coefficients
   int n_targets;             // bisector xi: T_{l nu} spectra
-  // midpoint P: A_{l nu} fields (l >= 2) and their forward pair jobs
-  int n_a;
-  std::vector<FieldJob> ajobs;
+  int n_a;                   // midpoint P: A_{l nu} fields (l >= 2)
   // bisector P: series orders of the one-pass per-order contraction (0: not available) and
   // the multipole of each of its result rows (beta * nell + l/2; -1 beyond zeroth order,
   // where no shot noise is subtracted)
@@ -162,7 +160,7 @@ struct DevPlan {
   WorkLayout work;
   std::vector<std::pair<void *, size_t>> allocs;
   void *tw = nullptr;
-  FieldJob *jobs = nullptr, *ijobs = nullptr, *ajobs = nullptr, *lean_jobs = nullptr;
+  FieldJob *jobs = nullptr, *ijobs = nullptr, *lean_jobs = nullptr;
   int *lean_fmap = nullptr;
   void *bufC = nullptr;  // memory-lean: y-pass output of one field group
   DevPrune fwd, sph;
