@@ -259,7 +259,7 @@ k_fziz(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ prod, cplx<R> *__re
       const __amdgpu_buffer_rsrc_t r = buf_rsrc(out + (size_t)(p - n_inplace) * nz * npen, out_bytes);
 #pragma unroll
       for (int s = 0; s < 8; ++s)
-        if (wstore >> s & 1) buf_store<R>(v[s], r, zo[s], 0);
+        if (wstore >> s & 1) buf_store<R, keep_lines(N) ? 0 : kNt>(v[s], r, zo[s], 0);
     }
   };
   // conj(D) / W^2 on every mode, D = d_scale Q_000~; field 0's own product is then

@@ -127,7 +127,7 @@ k_fx(const R *__restrict__ mesh, cplx<R> *__restrict__ out, const FieldJob *__re
     rowlist = bs.rowlist;
     norm = bs.norm;
   }
-  constexpr bool WAVE = (T == 64);
+  constexpr bool WAVE = (T == 64), NT = !keep_lines(N);
   constexpr int LN = N + N / 8;
   __shared__ cplx<R> lds[ROWS * LN];
   const int rl = threadIdx.x / T, t = threadIdx.x % T;
@@ -275,8 +275,8 @@ k_fx(const R *__restrict__ mesh, cplx<R> *__restrict__ out, const FieldJob *__re
         const int kx = t + 64 * s;
         if (kx < rs) {
           const bool keep = kx < nkx;
-          oa[kx] = keep ? mk<R>(a.x + b.x, a.y - b.y) : mk<R>(0, 0);
-          if (hb) ob[kx] = keep ? mk<R>(a.y + b.y, b.x - a.x) : mk<R>(0, 0);
+          store_nt<NT>(oa + kx, keep ? mk<R>(a.x + b.x, a.y - b.y) : mk<R>(0, 0));
+          if (hb) store_nt<NT>(ob + kx, keep ? mk<R>(a.y + b.y, b.x - a.x) : mk<R>(0, 0));
         }
       }
       const int kx = 256 + t;
@@ -297,8 +297,8 @@ k_fx(const R *__restrict__ mesh, cplx<R> *__restrict__ out, const FieldJob *__re
           continue;
         }
         const cplx<R> a = at(kx), b = at((N - kx) & (N - 1));
-        oa[kx] = mk<R>(a.x + b.x, a.y - b.y);
-        if (hb) ob[kx] = mk<R>(a.y + b.y, b.x - a.x);
+        store_nt<NT>(oa + kx, mk<R>(a.x + b.x, a.y - b.y));
+        if (hb) store_nt<NT>(ob + kx, mk<R>(a.y + b.y, b.x - a.x));
       }
       __syncthreads();
     }
@@ -438,7 +438,7 @@ k_fy(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, int nfields, int
     for (int s = 0; s < 8; ++s) {
       // whole 128-byte lines: the row's padding slots are written too (never read as modes)
       const bool keep = kx < yl[s];
-      if (__builtin_amdgcn_ballot_w64(keep)) buf_store<R>(v[s], w, keep ? so[s] : kOob, 0);
+      if (__builtin_amdgcn_ballot_w64(keep)) buf_store<R, keep_lines(N) ? 0 : kNt>(v[s], w, keep ? so[s] : kOob, 0);
     }
   }
 }
@@ -548,7 +548,7 @@ k_fz(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, int nfields, int
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
       const int z = t + s * T;
-      v[s] = (has && msk[z]) ? src[(size_t)z * npen + q] : mk<R>(0, 0);
+      v[s] = (has && msk[z]) ? load_nt(src + (size_t)z * npen + q) : mk<R>(0, 0);
     }
   };
   int lb = 0;
@@ -580,14 +580,14 @@ k_fz(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, int nfields, int
       cplx<R> *dst = out + (size_t)(fmap ? fmap[p] : p) * mstride + m0 + c;
 #pragma unroll
       for (int s = 0; s < 8; ++s)
-        if (slot[s] >= 0) dst[(size_t)slot[s] * C] = v[s];
+        if (slot[s] >= 0) store_nt<!keep_lines(N)>(dst + (size_t)slot[s] * C, v[s]);
     } else {
 #pragma unroll
       for (int s = 0; s < 8; ++s) at(t + s * T) = v[s];
       __syncthreads();
       // the block's pencils own one contiguous run of modes starting at m0, all N kz each
       cplx<R> *dst = out + (size_t)p * mstride + m0 + obase;
-      for (int j = oj; j < ocnt; j += T) dst[j] = lds[j * (C + 1) + oc];
+      for (int j = oj; j < ocnt; j += T) store_nt<!keep_lines(N)>(dst + j, lds[j * (C + 1) + oc]);
       __syncthreads();  // LDS reads done before the next transform writes
     }
   }
