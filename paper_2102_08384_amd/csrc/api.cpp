@@ -983,8 +983,6 @@ DevPlan *launch_estimate(pw_ctx *ctx, Lane &ln, const pw_config *cfg, const pw_c
   } else {
     // Full sets: pencil q = ky * rs + kx, N values each (bisector xi: the z-pass spectra in A,
     // pencil-major [p][q * N + kz]; midpoint: the y-pass output in B, [p][z][q]).
-    const double sfull = (double)N * N * F.nkx * csz;  // one full half spectrum (algorithmic)
-    const size_t sfull_b = (size_t)N * F.npen * (size_t)csz;  // one full pencil-major spectrum
     const double inv_n3 = 1.0 / ncell;
     const int npl = h.nz;  // retained z planes (= y rows) of the inverse outputs
     const double zpart = (double)h.n_inv * npl * F.npen_real * csz;
@@ -1005,15 +1003,18 @@ DevPlan *launch_estimate(pw_ctx *ctx, Lane &ln, const pw_config *cfg, const pw_c
     } else {
       // a4 z pass + a5: conj(D) Q / W^2 (D = sqrt(4 pi) Q_{0,0,0}) + inverse z pass, one kernel
       // from the y-pass output (B): the alpha = 0 products of P_l stay in k-space at the front
-      // of A, the retained z planes of the others follow them
-      zout = A + (size_t)h.n_inplace * sfull_b;
+      // of A (real parts on the k-sphere of the bins), the retained z planes of the others follow
+      zout = A + front_bytes(h);
+      SphereSet sph;
+      sph.ycnt = dp->sph.ycnt; sph.yoff = dp->sph.yoff; sph.goff = dp->sph.goff; sph.gsize = dp->sph.gsize;
+      sph.mstride = h.sph.mstride;
       // the fused kernel addresses one field with 32-bit byte offsets below 2^31 (its masked
       // lanes use offset 2^31); with N <= 512 a field is at most 1.2 GB
       if ((double)N * F.npen * csz >= 2147483648.0) fail(PW_EINVAL, "field too large for the fused z pass");
-      mark("fziz", x2 + (double)h.n_inplace * sfull + zpart);
+      mark("fziz", x2 + (double)h.n_inplace * h.sph.nretained * rsz + zpart);
       tuned_launch(ctx, ln, tune_key("fziz", h, h.nfields, h.n_inplace, npl), fz_candidates(h.nfields),
                    [&](ColTune t) {
-                     launch_fziz(s, h.prec, N, B, A, zout, h.nfields, h.n_inplace, F.npen, F.rs, sqrt4pi, dp->winv,
+                     launch_fziz(s, h.prec, N, B, A, sph, zout, h.nfields, h.n_inplace, F.npen, F.rs, sqrt4pi, dp->winv,
                                  dp->zrank, npl, dp->tw, dp->planemask, t);
                    });
     }
@@ -1032,14 +1033,14 @@ DevPlan *launch_estimate(pw_ctx *ctx, Lane &ln, const pw_config *cfg, const pw_c
       mark("finalize", 0.0);
       launch_finalize_xi(s, dp->acc, h.nell, h.n_bins, h.H * h.H * h.H, dp->norm, dp->out);
     } else {
-      void *Aoff = A + (size_t)h.n_inplace * sfull_b;  // behind the alpha = 0 products
+      void *Aoff = A + front_bytes(h);  // behind the alpha = 0 products
       if (h.n_inv > 0) {
         // a6: the g fields' inverse x pass, A_{l nu} = sum Phi' y(D^) |D|^alpha g and the forward x
         // pass of A in one kernel, then A's y and z passes, pruned to the k-sphere of the bins
         // (ending in Aoff)
         const Prune &P = h.sph;
         const double a1 = (double)h.n_a * N * N * P.nkx * csz, a2 = (double)h.n_a * N * P.npen * csz,
-                     a3 = (double)h.n_a * P.nretained * csz;
+                     a3 = (double)h.n_a * P.nretained * rsz;
         mark("mix", ypart + a1);
         launch_mix(s, h.prec, N, h.ell_max, h.order, h.all_parity, yout, Aoff, F.rs, P.nkx, P.rs, inv_n3,
                    h.H / h.unit, dp->tw);
@@ -1050,12 +1051,12 @@ DevPlan *launch_estimate(pw_ctx *ctx, Lane &ln, const pw_config *cfg, const pw_c
         mark("afz", a2 + a3);
         if (P.npen > 0)
           launch_fz(s, h.prec, N, B, Aoff, h.n_a, P.npen, dp->sph.pinfo, dp->sph.moff, dp->sph.goff, dp->sph.gsize,
-                    P.mstride, dp->tw, nullptr);
+                    P.mstride, dp->tw, nullptr, nullptr, ColTune(), nullptr, true);
       }
       // a7 (midpoint): sum_nu y_l^nu(k^) Re[G_{l nu} + A_{l nu}] and FP64 k-binning
-      mark("contract", (double)(h.n0 + h.n_a) * h.sph.nretained * csz + 4.0 * h.sph.nretained);
+      mark("contract", (double)(h.n0 + h.n_a) * h.sph.nretained * rsz + 4.0 * h.sph.nretained);
       launch_fill(s, dp->acc, nacc, 1);
-      launch_contract_mid(s, h.prec, h.ell_max, A, F.rs, h.n_a > 0 ? Aoff : nullptr, h.sph.nmodes, h.sph.mstride,
+      launch_contract_mid(s, h.prec, h.ell_max, A, h.n_a > 0 ? Aoff : nullptr, h.sph.nmodes, h.sph.mstride,
                           dp->sph.modecoord, N, dp->bin_of_s2, n_s2, h.n_bins, h.kf, dp->acc);
       mark("finalize", 0.0);
       launch_finalize_pk(s, dp->acc, h.nell, h.n_bins, dp->ells, dp->norm, dp->out);

@@ -292,6 +292,14 @@ template <int COUNT, int I = 0, typename Fn> __device__ __forceinline__ void for
   }
 }
 
+template <typename R>
+__device__ __forceinline__ void buf_store_real(R x, __amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+  if constexpr (sizeof(R) == 4)
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, x), r, voff, soff, 0);
+  else
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, x), r, voff, soff, 0);
+}
+
 // Groups of fields per block (grid.y) for column passes, so that a launch has about 4096
 // blocks when the pencil dimension alone gives fewer.
 inline int field_groups(int nfields, int nblocks_other) {

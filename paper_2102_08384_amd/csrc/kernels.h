@@ -164,10 +164,12 @@ void launch_fy(hipStream_t s, int prec, int N, int inv, const void *in, void *ou
 // (C = 128 bytes / complex size, the pencils per workgroup).  Field stride mstride.
 // planemask (may be null): empty z-planes of the input are read as zeros.
 // fmap (may be null): the output field index of each input field p (sphere-pruned sets only)
+// real_only (sphere-pruned sets only): the real parts alone are stored, as reals in the same layout
 void launch_fz(hipStream_t s, int prec, int N, const void *in, void *out, int nfields,
                int64_t npen, const PencilInfo *pinfo, const int64_t *moff, const int64_t *goff,
                const int *gsize, int64_t mstride, const void *tw, const int *planemask,
-               const int *fmap = nullptr, ColTune tune = ColTune(), const Batch *batch = nullptr);
+               const int *fmap = nullptr, ColTune tune = ColTune(), const Batch *batch = nullptr,
+               bool real_only = false);
 
 // Bisector contraction + FP64 k-binning.
 struct TermTable {
@@ -217,12 +219,20 @@ int mid_reweight_nfields(int lmax, int order, int all_parity);
 void launch_iz(hipStream_t s, int prec, int N, void *in, void *out, int nfields, int n_inplace,
                int real_in, int64_t npen, int nkx, int rs, const void *D, double d_scale,
                const void *winv, const int *zrank, int nz, const void *tw);
+// A sphere-pruned set on the device (Prune): row lengths and offsets, group offsets and slot counts
+struct SphereSet {
+  const int *ycnt = nullptr;
+  const int64_t *yoff = nullptr, *goff = nullptr;
+  const int *gsize = nullptr;
+  int64_t mstride = 0;
+};
 // Midpoint g fields: forward z pass of the y-pass output in[p][z][q] (full sets), the product
-// conj(D) Q / W^2 with D = d_scale * (field 0's transform), then either the product stays
-// pencil-major in prod[p][q * N + kz] (p < n_inplace) or the inverse z pass writes the
-// retained planes out[p - n_inplace][zrank[z]][q].  planemask: z planes with data (others zero).
-void launch_fziz(hipStream_t s, int prec, int N, const void *in, void *prod, void *out, int nfields, int n_inplace,
-                 int64_t npen, int rs, double d_scale, const void *winv, const int *zrank, int nz, const void *tw,
+// conj(D) Q / W^2 with D = d_scale * (field 0's transform), then either the product's real part on
+// the sphere sph is stored, prod[p * sph.mstride + slot] (reals; p < n_inplace), or the inverse z
+// pass writes the retained planes out[p - n_inplace][zrank[z]][q].  planemask: z planes with data
+// (others zero).
+void launch_fziz(hipStream_t s, int prec, int N, const void *in, void *prod, const SphereSet &sph, void *out,
+                 int nfields, int n_inplace, int64_t npen, int rs, double d_scale, const void *winv, const int *zrank, int nz, const void *tw,
                  const int *planemask, ColTune tune = ColTune());
 // Inverse x pass (complex-to-real) of pair jobs on the rows (zr, yr) of in[p][zr][yr * rs + kx],
 // kx <= N/2, scaled by `scale`.
@@ -244,12 +254,13 @@ void launch_mix(hipStream_t s, int prec, int N, int lmax, int order, int all_par
 // Field p of spec starts at p * mstride; target t of T at t * nmodes.
 void launch_targets(hipStream_t s, int prec, int N, int lmax, int bmax, const void *spec, int64_t nmodes,
                     int64_t mstride, int rs, const void *winv, void *T);
-// Midpoint P contraction: E_l = sum_nu y_l^nu(k^) Re[G_{l nu}(k) + A_{l nu}(k)] on the k-sphere
-// modes; G: full pencil-major products (alpha = 0 fields, index even_index(l, nu)); A: pruned
-// spectra of the A fields (l >= 2, index even_index(l, nu) - 1; null when absent).
-void launch_contract_mid(hipStream_t s, int prec, int lmax, const void *G, int rs_full, const void *A,
-                         int64_t nmodes, int64_t mstride, const uint32_t *modecoord, int N, const int *bin_of_s2,
-                         int64_t n_s2, int nbins, double kf, double *acc);
+// Midpoint P contraction: E_l = sum_nu y_l^nu(k^) (G_{l nu}(k) + A_{l nu}(k)) on the k-sphere modes; G
+// and A hold the real parts in the sphere's layout (field stride mstride): G the alpha = 0 products
+// (index even_index(l, nu)), A the spectra of the A fields (l >= 2, index even_index(l, nu) - 1; null
+// when absent).
+void launch_contract_mid(hipStream_t s, int prec, int lmax, const void *G, const void *A, int64_t nmodes,
+                         int64_t mstride, const uint32_t *modecoord, int N, const int *bin_of_s2, int64_t n_s2,
+                         int nbins, double kf, double *acc);
 void launch_finalize_xi(hipStream_t s, const double *acc, int nell, int nbins, double cell_volume,
                         const DevNorm *norm, double *out);
 

@@ -498,7 +498,8 @@ void launch_fy(hipStream_t s, int prec, int N, int inv, const void *in, void *ou
 // Output layouts (see Prune): full sets pencil-major, written through an LDS transpose so that
 // each pencil's run leaves as whole wavefront stores; sphere-pruned sets (goff != null) grouped
 // as [kz slot][pencil], so the C lanes of one kz write one 128-byte line straight from registers.
-template <typename R, int N, bool GROUPED>
+// (REAL_ONLY: the real parts alone, for spectra whose imaginary parts no shell sum reads)
+template <typename R, int N, bool GROUPED, bool REAL_ONLY>
 __global__ void __launch_bounds__((ColShape<R, N>::THREADS))
 k_fz(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, int nfields, int fpb, int64_t npen,
      const PencilInfo *__restrict__ pinfo, const int64_t *__restrict__ moff, const int64_t *__restrict__ goff,
@@ -577,10 +578,15 @@ k_fz(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, int nfields, int
     else fft_pencil<R, N, false>(v, t, twr, at, sync);
     if constexpr (GROUPED) {
       // fmap: output field of input field p (a group of fields transformed at a time)
-      cplx<R> *dst = out + (size_t)(fmap ? fmap[p] : p) * mstride + m0 + c;
+      const size_t o = (size_t)(fmap ? fmap[p] : p) * mstride + m0 + c;
+      cplx<R> *dst = out + o;
+      R *rdst = reinterpret_cast<R *>(out) + o;
 #pragma unroll
       for (int s = 0; s < 8; ++s)
-        if (slot[s] >= 0) store_nt<!keep_lines(N)>(dst + (size_t)slot[s] * C, v[s]);
+        if (slot[s] >= 0) {
+          if constexpr (REAL_ONLY) rdst[(size_t)slot[s] * C] = v[s].x;
+          else store_nt<!keep_lines(N)>(dst + (size_t)slot[s] * C, v[s]);
+        }
     } else {
 #pragma unroll
       for (int s = 0; s < 8; ++s) at(t + s * T) = v[s];
@@ -597,7 +603,7 @@ template <typename R, int N>
 static void fz_launch(hipStream_t s, const void *in, void *out, int nfields, int64_t npen,
                       const PencilInfo *pinfo, const int64_t *moff, const int64_t *goff, const int *gsize,
                       int64_t mstride, const void *tw, const int *planemask, const int *fmap,
-                      ColTune tune, const Batch *batch) {
+                      ColTune tune, const Batch *batch, bool real_only) {
   constexpr int C = ColShape<R, N>::C;
   static_assert(C == 128 / (int)sizeof(cplx<R>), "z-pass groups must match 128-byte slot rows");
   const unsigned ng = (unsigned)((npen + C - 1) / C);
@@ -612,12 +618,16 @@ static void fz_launch(hipStream_t s, const void *in, void *out, int nfields, int
   }
   fpb = std::min(fpb, nfields);
   dim3 grid(ng, (nfields + fpb - 1) / fpb, nb);
-  if (goff)
-    hipLaunchKernelGGL((k_fz<R, N, true>), grid, dim3(ColShape<R, N>::THREADS), 0, s, (const cplx<R> *)in,
+  if (goff && real_only)
+    hipLaunchKernelGGL((k_fz<R, N, true, true>), grid, dim3(ColShape<R, N>::THREADS), 0, s, (const cplx<R> *)in,
+                       (cplx<R> *)out, nfields, fpb, npen, pinfo, moff, goff, gsize, mstride, (const cplx<R> *)tw,
+                       planemask, fmap, ba);
+  else if (goff)
+    hipLaunchKernelGGL((k_fz<R, N, true, false>), grid, dim3(ColShape<R, N>::THREADS), 0, s, (const cplx<R> *)in,
                        (cplx<R> *)out, nfields, fpb, npen, pinfo, moff, goff, gsize, mstride, (const cplx<R> *)tw,
                        planemask, fmap, ba);
   else
-    hipLaunchKernelGGL((k_fz<R, N, false>), grid, dim3(ColShape<R, N>::THREADS), 0, s, (const cplx<R> *)in,
+    hipLaunchKernelGGL((k_fz<R, N, false, false>), grid, dim3(ColShape<R, N>::THREADS), 0, s, (const cplx<R> *)in,
                        (cplx<R> *)out, nfields, fpb, npen, pinfo, moff, goff, gsize, mstride, (const cplx<R> *)tw,
                        planemask, (const int *)nullptr, ba);
 }
@@ -625,14 +635,14 @@ static void fz_launch(hipStream_t s, const void *in, void *out, int nfields, int
 void launch_fz(hipStream_t s, int prec, int N, const void *in, void *out, int nfields, int64_t npen,
                const PencilInfo *pinfo, const int64_t *moff, const int64_t *goff, const int *gsize,
                int64_t mstride, const void *tw, const int *planemask, const int *fmap, ColTune tune,
-               const Batch *batch) {
+               const Batch *batch, bool real_only) {
   if (nfields <= 0 || npen <= 0) return;
   if (prec == 0) {
     PW_DISPATCH_N(fz_launch, float, s, in, out, nfields, npen, pinfo, moff, goff, gsize, mstride, tw, planemask,
-                  fmap, tune, batch)
+                  fmap, tune, batch, real_only)
   } else {
     PW_DISPATCH_N(fz_launch, double, s, in, out, nfields, npen, pinfo, moff, goff, gsize, mstride, tw, planemask,
-                  fmap, tune, batch)
+                  fmap, tune, batch, real_only)
   }
 }
 

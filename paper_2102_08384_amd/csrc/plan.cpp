@@ -458,13 +458,17 @@ HostPlan build_host_plan(const pw_config &c) {
   if (h.path == PATH_MID_PK && h.n_a > 0) {
     // buffer A: the alpha = 0 products, then a region (avail) that holds in turn the retained z
     // planes and the A fields' x-pass and z-pass outputs; B holds the y-pass outputs
-    const size_t sfull = (size_t)N * h.fwd.npen * csz, sb = spectrum_buffer_bytes(h);
-    const size_t front = (size_t)h.n_inplace * sfull, avail = sb > front ? sb - front : 0;
+    const size_t sb = spectrum_buffer_bytes(h), front = front_bytes(h), avail = sb > front ? sb - front : 0;
     if ((size_t)h.n_inv * h.nz * h.fwd.npen * csz > avail || (size_t)h.n_a * N * N * h.sph.rs * csz > avail ||
         (size_t)h.n_a * h.sph.mstride * csz > avail)
       plan_fail(PW_EINVAL, "internal: A fields do not fit the spectrum buffer");
   }
   return h;
+}
+
+size_t front_bytes(const HostPlan &h) {
+  const size_t rsz = h.prec == PW_FP32 ? 4 : 8;
+  return ((size_t)h.n_inplace * h.sph.mstride * rsz + 255) & ~(size_t)255;
 }
 
 size_t spectrum_buffer_bytes(const HostPlan &h) {

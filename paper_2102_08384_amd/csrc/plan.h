@@ -141,6 +141,8 @@ size_t catalog_bytes(const pw_config &c, const pw_catalog &gal, const pw_catalog
 size_t records_bytes(int prec, int64_t n_gal, int64_t n_ran);
 // bytes of each of the two spectrum buffers (memory-lean: of the k-sphere buffer)
 size_t spectrum_buffer_bytes(const HostPlan &h);
+// midpoint P_l: the alpha = 0 products at the front of buffer A
+size_t front_bytes(const HostPlan &h);
 // memory-lean bisector: x-pass and y-pass work buffers of one field group
 size_t lean_x_bytes(const HostPlan &h);
 size_t lean_y_bytes(const HostPlan &h);
