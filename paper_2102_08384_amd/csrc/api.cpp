@@ -492,6 +492,7 @@ std::unique_ptr<DevPlan> build_dev_plan(pw_ctx *ctx, const pw_config *cfg, char 
     dp->zidx = upload(M, h.zidx);
     dp->yidx = upload(M, h.yidx);
     dp->iycnt = upload(M, h.iycnt);
+    dp->odd_of = upload(M, h.odd_of);
     dp->iyoff = upload(M, h.iyoff);
     auto up_real = [&](const std::vector<double> &v) -> void * {
       if (h.prec == PW_FP32) {
@@ -984,7 +985,7 @@ DevPlan *launch_estimate(pw_ctx *ctx, Lane &ln, const pw_config *cfg, const pw_c
     // Full sets: pencil q = ky * rs + kx, N values each (bisector xi: the z-pass spectra in A,
     // pencil-major [p][q * N + kz]; midpoint: the y-pass output in B, [p][z][q]).
     const double inv_n3 = 1.0 / ncell;
-    const int npl = h.nz;  // retained z planes (= y rows) of the inverse outputs
+    const int npl = h.nz;  // retained z planes of the inverse outputs
     const double zpart = (double)h.n_inv * npl * F.npen_real * csz;
     const double ypart = (double)h.n_inv * npl * h.ny * F.nkx * csz;
     const bool xi = h.path != PATH_MID_PK;
@@ -998,8 +999,7 @@ DevPlan *launch_estimate(pw_ctx *ctx, Lane &ln, const pw_config *cfg, const pw_c
       launch_targets(s, h.prec, N, h.ell_max, h.order / 2, A, F.nmodes, F.mstride, F.rs, dp->winv, B);
       zout = A;
       mark("iz", (double)h.n_targets * modes_real * rsz + zpart);
-      launch_iz(s, h.prec, N, B, zout, h.n_targets, 0, 1, F.npen, F.nkx, F.rs, nullptr, sqrt4pi, nullptr,
-                dp->zrank, npl, dp->tw);
+      launch_iz(s, h.prec, N, B, zout, h.n_targets, F.npen, npl, dp->tw);
     } else {
       // a4 z pass + a5: conj(D) Q / W^2 (D = sqrt(4 pi) Q_{0,0,0}) + inverse z pass, one kernel
       // from the y-pass output (B): the alpha = 0 products of P_l stay in k-space at the front
@@ -1014,6 +1014,11 @@ DevPlan *launch_estimate(pw_ctx *ctx, Lane &ln, const pw_config *cfg, const pw_c
       mark("fziz", x2 + (double)h.n_inplace * h.sph.nretained * rsz + zpart);
       tuned_launch(ctx, ln, tune_key("fziz", h, h.nfields, h.n_inplace, npl), fz_candidates(h.nfields),
                    [&](ColTune t) {
+                     if (h.half) {
+                       launch_fziz_half(s, h.prec, N, B, zout, h.nfields, F.npen, F.rs, sqrt4pi, dp->winv, dp->odd_of,
+                                        npl, dp->tw, dp->planemask, t);
+                       return;
+                     }
                      launch_fziz(s, h.prec, N, B, A, sph, zout, h.nfields, h.n_inplace, F.npen, F.rs, sqrt4pi, dp->winv,
                                  dp->zrank, npl, dp->tw, dp->planemask, t);
                    });
@@ -1028,7 +1033,7 @@ DevPlan *launch_estimate(pw_ctx *ctx, Lane &ln, const pw_config *cfg, const pw_c
     if (xi) {
       // a8: c2r along x fused with the |D|^alpha y(D^) weighting and FP64 r-binning
       mark("ix_bin", ypart);
-      launch_ix(s, h.prec, N, yout, F.rs, dp->ijobs, (int)h.ijobs.size(), dp->icoef, h.nell, h.nz, h.ny,
+      launch_ix(s, h.prec, N, yout, F.rs, dp->ijobs, (int)h.ijobs.size(), dp->icoef, h.nell, h.half, h.nz, h.ny,
                 dp->zidx, dp->yidx, h.H, h.unit, inv_n3, dp->bin_of_s2, n_s2, h.n_bins, dp->acc, dp->tw);
       mark("finalize", 0.0);
       launch_finalize_xi(s, dp->acc, h.nell, h.n_bins, h.H * h.H * h.H, dp->norm, dp->out);

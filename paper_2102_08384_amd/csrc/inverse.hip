@@ -1,9 +1,11 @@
 // HIP kernels of the inverse-transform paths (gfx950, wave64).
 //
-//   iz             inverse FFT along z of full pencil-major spectra (bisector xi_l targets);
-//                  output pruned to the retained z planes
+//   iz             bisector xi_l: inverse FFT along z of the real targets, pencil-major, two to a
+//                  transform; output pruned to the retained planes z >= 0
 //   fziz           midpoint g fields: forward FFT along z, the product conj(D) Q / W^2
 //                  (Section 3.2) and the inverse FFT along z in one pass over each pencil
+//   fziz_half      the same for xi_l, whose sums need only the part of g that is even (or odd) in D:
+//                  two fields to an inverse transform, planes z >= 0
 //   ix             xi_l: complex-to-real inverse FFT along x of field pairs, weighted by
 //                  |D|^alpha y_J^mu(D^) times the per-field multipole coefficient and binned into
 //                  r-shells in FP64 (Section 4.3 midpoint estimator, Section 6 bisector estimator)
@@ -12,6 +14,7 @@
 //   finalize_xi    xi_l = (4 pi / I) sum / (N_a H^3)
 #include "kernels.h"
 
+#include <algorithm>
 #include <type_traits>
 
 #include "dev_core.h"
@@ -24,12 +27,44 @@ void upload_sh_const_inverse(const ShConst &c) {
   (void)hipMemcpyToSymbol(HIP_SYMBOL(c_sh_inv), &c, sizeof(ShConst));
 }
 
-// ------------------------------------------------------------------------------ iz
-template <typename R, int N, bool REAL_IN>
+// ------------------------------------------------------------------------------ half sets
+// xi_l sums w_f(D) g_f(D) over whole shells of separations, D and -D alike, and every weight
+// |D|^alpha y_J^mu(D^) has the parity of J: only the part of g of that parity counts, and the half
+// z >= 0 of the separations, counted twice off the self-mirrored planes z = 0 and z = N/2, holds it.
+// The even part's spectrum is Re G, the odd part's i Im G, so one complex transform along z carries
+// two fields: with Z = IFT[s_a + i s_b] of real s_a, s_b (s = Re G or Im G, each scaled by 1/2),
+//   h_a(z) = Z(z) + conj Z(-z),  h_b(z) = -i (Z(z) - conj Z(-z)),
+// and an odd field's h is multiplied by i.
 
+// On entry lane t holds v[s] = Z(t + s T); `at` is this pencil's LDS row, free on entry and on exit
+// (the caller's next exchange comes after the closing barrier).  fn(s, z, h_a, h_b) is called for
+// the planes z = t + s T <= zmax of this lane.
+template <typename R, int T, int N, typename At, typename Fn>
+__device__ __forceinline__ void split_half(const cplx<R> v[8], int t, int zmax, At at, Fn fn) {
+#pragma unroll
+  for (int s = 3; s < 8; ++s) {  // mirrors of 1 .. N/2
+    const int z = t + s * T;
+    if (z >= N / 2 && N - z <= zmax) at(z) = v[s];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int s = 0; s < 5; ++s) {
+    const int z = t + s * T;
+    if (z <= zmax && z <= N / 2) {
+      const cplx<R> w = z == 0 ? v[0] : at(N - z);
+      fn(s, z, mk<R>(v[s].x + w.x, v[s].y - w.y), mk<R>(v[s].y + w.y, w.x - v[s].x));
+    }
+  }
+  __syncthreads();
+}
+
+// ------------------------------------------------------------------------------ iz
+// Bisector targets are real, T(-k) = T(k): Z = IFT[(T_a + i T_b) / 2], bound by the read of the targets
+// and the exchanges' barriers.  Two targets to a transform and half the planes, through this pass and
+// the inverse y and x passes: a bisector xi_l of 512^3 went from 25.8 to 25.0 ms.
+template <typename R, int N>
 __global__ void __launch_bounds__((ColShape<R, N>::THREADS))
-k_iz(cplx<R> *in, const R *in_real, cplx<R> *__restrict__ out, int nfields, int n_inplace, int64_t npen,
-     int nkx, int rs, const cplx<R> *D, R d_scale, const R *__restrict__ winv, const int *__restrict__ zrank, int nz,
+k_iz(const R *__restrict__ in, cplx<R> *__restrict__ out, int nfields, int64_t npen, int nz,
      const cplx<R> *__restrict__ tw) {
   constexpr int T = ColShape<R, N>::T, C = ColShape<R, N>::C, NT = ColShape<R, N>::THREADS;
   constexpr int LOGN = log2i(N);
@@ -45,132 +80,57 @@ k_iz(cplx<R> *in, const R *in_real, cplx<R> *__restrict__ out, int nfields, int 
   twr.load(t, tw);
   wait_vmem();
   const size_t fstride = (size_t)npen * N;
-  // the chunk of pencils q0 .. q0 + C - 1 is contiguous: element e = cc * N + kz
-  auto load_chunk = [&](const cplx<R> *src) {
-    for (int e = threadIdx.x; e < C * N; e += NT) {
-      const int cc = e >> LOGN, kz = e & (N - 1);
-      lds[kz * (C + 1) + cc] = (e < nval) ? src[(size_t)q0 * N + e] : mk<R>(0, 0);
-    }
-  };
-  // full retention: pencil q = ky * rs + kx (kx >= nkx: all-zero padding pencils)
-  const int qky = (int)(q / rs), qkx = (int)(q - (int64_t)qky * rs);
-  const int64_t qo = q;
-  const int64_t plane_o = npen;
-  cplx<R> dv[8];
-  if (!REAL_IN && D) {
-    load_chunk(D);
-    sync();
-    R iwxy = (R)1;
-    if (winv && q < npen) iwxy = winv[qkx] * winv[qky];
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      const int kz = t + s * T;
-      R f = d_scale;
-      if (winv) {
-        const R iw = iwxy * winv[kz];
-        f *= iw * iw;
-      }
-      const cplx<R> d = at(kz);
-      dv[s] = mk<R>(d.x * f, -d.y * f);
-    }
-    sync();
-  }
-  // each field's chunk: PER values per thread, loaded together into registers, then placed in
-  // LDS; real inputs (held as reals: half the registers) load the next field's chunk while the
-  // current one is transformed
+  // the pair's chunks (pencils q0 .. q0 + C - 1, contiguous: element e = cc * N + kz): PER values per
+  // thread, the next pair's loaded while the current one is transformed
   constexpr int PER = C * N / NT;
-  typedef typename std::conditional<REAL_IN, R, cplx<R>>::type In;
-  auto fetch = [&](int p, In *x) {
+  R xa[PER], xb[PER];
+  auto fetch = [&](int p) {
+    const R *src = in + (size_t)p * fstride + (size_t)q0 * N;
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
       const int e = threadIdx.x + k * NT;
-      if constexpr (REAL_IN) {
-        const R *src = in_real + (size_t)p * fstride;
-        x[k] = (e < nval) ? src[(size_t)q0 * N + e] : (R)0;
-      } else {
-        const cplx<R> *src = in + (size_t)p * fstride;
-        x[k] = (e < nval) ? src[(size_t)q0 * N + e] : mk<R>(0, 0);
-      }
+      xa[k] = e < nval ? __builtin_nontemporal_load(src + e) : (R)0;
+      xb[k] = (e < nval && p + 1 < nfields) ? __builtin_nontemporal_load(src + fstride + e) : (R)0;
     }
   };
-  // output plane of every kz (-1: not kept), read once into LDS
-  __shared__ int zsh[N];
-  for (int i = threadIdx.x; i < N; i += NT) zsh[i] = zrank[i];
-  In xb[PER];
-  if constexpr (REAL_IN) {
-    if (nfields > 0) fetch(0, xb);
-  }
-  for (int p = 0; p < nfields; ++p) {
-    if constexpr (!REAL_IN) fetch(p, xb);
+  fetch(0);
+  for (int p = 0; p < nfields; p += 2) {
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
       const int e = threadIdx.x + k * NT;
-      if constexpr (REAL_IN) lds[(e & (N - 1)) * (C + 1) + (e >> LOGN)] = mk<R>(xb[k], (R)0);
-      else lds[(e & (N - 1)) * (C + 1) + (e >> LOGN)] = xb[k];
+      lds[(e & (N - 1)) * (C + 1) + (e >> LOGN)] = mk<R>((R)0.5 * xa[k], (R)0.5 * xb[k]);
     }
     sync();
     cplx<R> v[8];
 #pragma unroll
     for (int s = 0; s < 8; ++s) v[s] = at(t + s * T);
-    if (!REAL_IN && D) {
-#pragma unroll
-      for (int s = 0; s < 8; ++s) v[s] = cmul(dv[s], v[s]);
-    }
     sync();
-    if constexpr (REAL_IN) {
-      if (p + 1 < nfields) fetch(p + 1, xb);
-    }
-    if (p < n_inplace) {
-      // the product stays in k-space: store it back in place, coalesced through LDS
-#pragma unroll
-      for (int s = 0; s < 8; ++s) at(t + s * T) = v[s];
-      sync();
-      cplx<R> *dst = in + (size_t)p * fstride;
-      for (int e = threadIdx.x; e < nval; e += NT) {
-        const int cc = e >> LOGN, kz = e & (N - 1);
-        dst[(size_t)q0 * N + e] = lds[kz * (C + 1) + cc];
-      }
-      sync();
-      continue;
-    }
+    if (p + 2 < nfields) fetch(p + 2);
     fft_pencil<R, N, true>(v, t, twr, at, sync);
-    if (q < npen) {
-      cplx<R> *dst = out + (size_t)(p - n_inplace) * nz * plane_o;
-#pragma unroll
-      for (int s = 0; s < 8; ++s) {
-        const int zr = zsh[t + s * T];
-        if (zr >= 0) dst[(size_t)zr * plane_o + qo] = v[s];
-      }
-    }
+    cplx<R> *oa = out + (size_t)p * nz * npen + q, *ob = oa + (size_t)nz * npen;
+    const bool two = p + 1 < nfields;
+    split_half<R, T, N>(v, t, nz - 1, at, [&](int, int z, cplx<R> ha, cplx<R> hb) {
+      if (q >= npen) return;
+      oa[(size_t)z * npen] = ha;
+      if (two) ob[(size_t)z * npen] = hb;
+    });
   }
 }
 
 template <typename R, int N>
-static void iz_launch(hipStream_t s, void *in, void *out, int nfields, int n_inplace, int real_in, int64_t npen,
-                      int nkx, int rs, const void *D, double d_scale, const void *winv, const int *zrank, int nz,
-                      const void *tw) {
+static void iz_launch(hipStream_t s, const void *in, void *out, int nfields, int64_t npen, int nz, const void *tw) {
   constexpr int C = ColShape<R, N>::C;
-  dim3 grid((unsigned)((npen + C - 1) / C));
-  if (real_in)
-    hipLaunchKernelGGL((k_iz<R, N, true>), grid, dim3(ColShape<R, N>::THREADS), 0, s, (cplx<R> *)nullptr,
-                       (const R *)in, (cplx<R> *)out, nfields, n_inplace, npen, nkx, rs, (const cplx<R> *)D,
-                       (R)d_scale, (const R *)winv, zrank, nz, (const cplx<R> *)tw);
-  else
-    hipLaunchKernelGGL((k_iz<R, N, false>), grid, dim3(ColShape<R, N>::THREADS), 0, s, (cplx<R> *)in,
-                       (const R *)nullptr, (cplx<R> *)out, nfields, n_inplace, npen, nkx, rs, (const cplx<R> *)D,
-                       (R)d_scale, (const R *)winv, zrank, nz, (const cplx<R> *)tw);
+  hipLaunchKernelGGL((k_iz<R, N>), dim3((unsigned)((npen + C - 1) / C)), dim3(ColShape<R, N>::THREADS), 0, s,
+                     (const R *)in, (cplx<R> *)out, nfields, npen, nz, (const cplx<R> *)tw);
 }
 
-void launch_iz(hipStream_t s, int prec, int N, void *in, void *out, int nfields, int n_inplace, int real_in,
-               int64_t npen, int nkx, int rs, const void *D, double d_scale, const void *winv, const int *zrank,
-               int nz, const void *tw) {
+void launch_iz(hipStream_t s, int prec, int N, const void *in, void *out, int nfields, int64_t npen, int nz,
+               const void *tw) {
   if (nfields <= 0 || npen <= 0) return;
   if (prec == 0) {
-    PW_DISPATCH_N(iz_launch, float, s, in, out, nfields, n_inplace, real_in, npen, nkx, rs, D, d_scale, winv,
-                  zrank, nz, tw)
+    PW_DISPATCH_N(iz_launch, float, s, in, out, nfields, npen, nz, tw)
   } else {
-    PW_DISPATCH_N(iz_launch, double, s, in, out, nfields, n_inplace, real_in, npen, nkx, rs, D, d_scale, winv,
-                  zrank, nz, tw)
+    PW_DISPATCH_N(iz_launch, double, s, in, out, nfields, npen, nz, tw)
   }
 }
 
@@ -341,13 +301,142 @@ void launch_fziz(hipStream_t s, int prec, int N, const void *in, void *prod, con
   }
 }
 
+// ------------------------------------------------------------------------------ fziz_half
+// k_fziz for xi_l (see half sets): fields p, p + 1 are transformed forward and multiplied by
+// conj(D) / W^2 one after the other, the real (imaginary: odd_of[p] != 0) parts kept, and go back
+// together.  Three transforms for two fields in place of four, and half the planes stored.  The pass
+// is bound by its VALU work: at 512^3 (FP32, 88 fields, 36 planes) 13.6 -> 11.5 ms, with the inverse y
+// and x passes after it 1.56 -> 0.82 and 1.21 -> 0.73 ms.
+template <typename R, int N>
+__global__ void __launch_bounds__((ColShape<R, N>::THREADS))
+k_fziz_half(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, int nfields, int fpb, int64_t npen, int rs,
+            R d_scale, const R *__restrict__ winv, const int *__restrict__ odd_of, int nz,
+            const cplx<R> *__restrict__ tw, const int *__restrict__ planemask) {
+  constexpr int T = ColShape<R, N>::T, C = ColShape<R, N>::C, NT = ColShape<R, N>::THREADS;
+  constexpr int64_t E = sizeof(cplx<R>);
+  __shared__ cplx<R> lds[N * (C + 1)];
+  __shared__ cplx<R> dls[8 * NT];  // each lane its own 8 values of conj(D) / W^2
+  const int c = threadIdx.x % C, t = threadIdx.x / C;
+  const int64_t q = (int64_t)blockIdx.x * C + c;
+  const int p0 = blockIdx.y * fpb;
+  const int p1 = min(nfields, p0 + fpb);
+  if (p0 >= p1) return;  // uniform
+  FftTw<R, N> twr;
+  twr.load(t, tw);
+  const bool has = q < npen;
+  // input planes as in k_fziz: byte offsets fixed for the kernel, empty planes out of range
+  const uint32_t sT = (uint32_t)(T * npen * E);
+  const uint32_t lane_in = (uint32_t)((t * npen + q) * E);
+  uint32_t lo[8], wload = 0;
+#pragma unroll
+  for (int s = 0; s < 8; ++s) {
+    lo[s] = (has && (!planemask || planemask[t + s * T])) ? lane_in : kOob;
+    if (__builtin_amdgcn_ballot_w64(lo[s] != kOob)) wload |= 1u << s;
+  }
+  const uint32_t in_bytes = (uint32_t)(N * npen * E), out_bytes = (uint32_t)(nz * npen * E);
+  R iwxy = (R)1;
+  if (winv && has) {
+    const int qky = (int)(q / rs), qkx = (int)(q - (int64_t)qky * rs);
+    iwxy = winv[qkx] * winv[qky];
+  }
+  wait_vmem();
+  auto load = [&](int p, cplx<R> *v) {
+    const __amdgpu_buffer_rsrc_t r = buf_rsrc(in + (size_t)p * N * npen, in_bytes);
+#pragma unroll
+    for (int s = 0; s < 8; ++s) v[s] = (wload >> s & 1) ? buf_load<R>(r, lo[s], (uint32_t)s * sT) : mk<R>(0, 0);
+  };
+  auto at = [c](int i) -> cplx<R> & { return lds[i * (C + 1) + c]; };
+  auto sync = []() { __syncthreads(); };
+  cplx<R> nxt[8];
+  {
+    cplx<R> d[8];
+    load(0, d);
+    load(p0, nxt);
+    fft_pencil<R, N, false>(d, t, twr, at, sync);
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const R iw = iwxy * (winv ? winv[t + s * T] : (R)1);
+      const R f = (R)0.5 * d_scale * iw * iw;
+      dls[s * NT + threadIdx.x] = mk<R>(d[s].x * f, -d[s].y * f);
+    }
+  }
+  for (int p = p0; p < p1; p += 2) {
+    const bool two = p + 1 < p1;
+    const int odd_a = odd_of ? odd_of[p] : 0, odd_b = (odd_of && two) ? odd_of[p + 1] : 0;
+    cplx<R> v[8];
+    R sa[8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) v[s] = nxt[s];
+    if (two) load(p + 1, nxt);
+    fft_pencil<R, N, false>(v, t, twr, at, sync);
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const cplx<R> g = cmul(dls[s * NT + threadIdx.x], v[s]);
+      sa[s] = odd_a ? g.y : g.x;
+    }
+    if (two) {
+#pragma unroll
+      for (int s = 0; s < 8; ++s) v[s] = nxt[s];
+      if (p + 2 < p1) load(p + 2, nxt);
+      fft_pencil<R, N, false>(v, t, twr, at, sync);
+#pragma unroll
+      for (int s = 0; s < 8; ++s) {
+        const cplx<R> g = cmul(dls[s * NT + threadIdx.x], v[s]);
+        v[s] = mk<R>(sa[s], odd_b ? g.y : g.x);
+      }
+    } else {
+#pragma unroll
+      for (int s = 0; s < 8; ++s) v[s] = mk<R>(sa[s], (R)0);
+    }
+    fft_pencil<R, N, true>(v, t, twr, at, sync);
+    const __amdgpu_buffer_rsrc_t ra = buf_rsrc(out + (size_t)p * nz * npen, out_bytes);
+    const __amdgpu_buffer_rsrc_t rb = buf_rsrc(out + (size_t)(p + 1) * nz * npen, out_bytes);
+    split_half<R, T, N>(v, t, nz - 1, at, [&](int, int z, cplx<R> ha, cplx<R> hb) {
+      const uint32_t zo = has ? (uint32_t)((z * npen + q) * E) : kOob;
+      buf_store<R, keep_lines(N) ? 0 : kNt>(odd_a ? mk<R>(-ha.y, ha.x) : ha, ra, zo, 0);
+      if (two) buf_store<R, keep_lines(N) ? 0 : kNt>(odd_b ? mk<R>(-hb.y, hb.x) : hb, rb, zo, 0);
+    });
+  }
+}
+
+template <typename R, int N>
+static void fziz_half_launch(hipStream_t s, const void *in, void *out, int nfields, int64_t npen, int rs,
+                             double d_scale, const void *winv, const int *odd_of, int nz, const void *tw,
+                             const int *planemask, ColTune tune) {
+  constexpr int C = ColShape<R, N>::C;
+  const unsigned ng = (unsigned)((npen + C - 1) / C);
+  int fpb = tune.fpb;
+  if (fpb <= 0) {
+    // (as in fziz_launch)
+    int G = field_groups(nfields, (int)std::min<int64_t>(ng, 1 << 20));
+    G = std::max(1, std::min(G, nfields / 8));
+    fpb = (nfields + G - 1) / G;
+  }
+  fpb = (std::min(fpb, nfields) + 1) / 2 * 2;  // whole pairs
+  dim3 grid(ng, (nfields + fpb - 1) / fpb);
+  hipLaunchKernelGGL((k_fziz_half<R, N>), grid, dim3(ColShape<R, N>::THREADS), 0, s, (const cplx<R> *)in,
+                     (cplx<R> *)out, nfields, fpb, npen, rs, (R)d_scale, (const R *)winv, odd_of, nz,
+                     (const cplx<R> *)tw, planemask);
+}
+
+void launch_fziz_half(hipStream_t s, int prec, int N, const void *in, void *out, int nfields, int64_t npen, int rs,
+                      double d_scale, const void *winv, const int *odd_of, int nz, const void *tw,
+                      const int *planemask, ColTune tune) {
+  if (nfields <= 0 || npen <= 0) return;
+  if (prec == 0) {
+    PW_DISPATCH_N(fziz_half_launch, float, s, in, out, nfields, npen, rs, d_scale, winv, odd_of, nz, tw, planemask, tune)
+  } else {
+    PW_DISPATCH_N(fziz_half_launch, double, s, in, out, nfields, npen, rs, d_scale, winv, odd_of, nz, tw, planemask, tune)
+  }
+}
+
 // ------------------------------------------------------------------------------ ix
 constexpr int kMaxEll = 5;  // multipoles 0, 2, .., 8
 
 template <typename R, int N>
 __global__ void __launch_bounds__(FxShape<N>::THREADS)
 k_ix(const cplx<R> *__restrict__ in, int rs, const FieldJob *__restrict__ jobs, int njobs,
-     const R *__restrict__ coef, int nell, int nz, int ny, const int *__restrict__ zidx,
+     const R *__restrict__ coef, int nell, int half, int nz, int ny, const int *__restrict__ zidx,
      const int *__restrict__ yidx, R Hu, double Hd, R scale, const int *__restrict__ bin_of_s2, int64_t n_s2,
      int nbins, double *__restrict__ acc, const cplx<R> *__restrict__ tw) {
   constexpr int T = FxShape<N>::T, ROWS = FxShape<N>::ROWS, NKX = N / 2 + 1;
@@ -457,6 +546,7 @@ k_ix(const cplx<R> *__restrict__ in, int rs, const FieldJob *__restrict__ jobs, 
     }
   }
   sync();  // bacc cleared by every thread before any accumulation
+  const double mult = (half && z != 0 && z != N / 2) ? 2.0 : 1.0;  // -D has the same terms
 #pragma unroll
   for (int s = 0; s < 8; ++s) {
     const int b = bin[s];
@@ -466,9 +556,9 @@ k_ix(const cplx<R> *__restrict__ in, int rs, const FieldJob *__restrict__ jobs, 
     const double s2 = (double)sx * sx + (double)sy * sy + (double)sz * sz;
 #pragma unroll
     for (int l = 0; l < kMaxEll; ++l)
-      if (l < nell) atomicAdd(&bacc[l * nbins + b], (double)(X[l][s] * scale));
-    atomicAdd(&bacc[nell * nbins + b], 1.0);
-    atomicAdd(&bacc[(nell + 1) * nbins + b], Hd * sqrt(s2));
+      if (l < nell) atomicAdd(&bacc[l * nbins + b], mult * (double)(X[l][s] * scale));
+    atomicAdd(&bacc[nell * nbins + b], mult);
+    atomicAdd(&bacc[(nell + 1) * nbins + b], mult * Hd * sqrt(s2));
   }
   sync();
   for (int i = threadIdx.x; i < nacc; i += blockDim.x)
@@ -477,26 +567,26 @@ k_ix(const cplx<R> *__restrict__ in, int rs, const FieldJob *__restrict__ jobs, 
 
 template <typename R, int N>
 static void ix_launch(hipStream_t s, const void *in, int rs, const FieldJob *jobs, int njobs, const void *coef,
-                      int nell, int nz, int ny, const int *zidx, const int *yidx, double H, double unit, double scale,
+                      int nell, int half, int nz, int ny, const int *zidx, const int *yidx, double H, double unit, double scale,
                       const int *bin_of_s2, int64_t n_s2, int nbins, double *acc, const void *tw) {
   constexpr int ROWS = FxShape<N>::ROWS;
   const int64_t nrows = (int64_t)nz * ny;
   dim3 grid((unsigned)((nrows + ROWS - 1) / ROWS));
   const size_t sh = (size_t)(nell + 2) * nbins * sizeof(double);
   hipLaunchKernelGGL((k_ix<R, N>), grid, dim3(FxShape<N>::THREADS), sh, s, (const cplx<R> *)in, rs, jobs, njobs,
-                     (const R *)coef, nell, nz, ny, zidx, yidx, (R)(H / unit), H, (R)scale, bin_of_s2, n_s2, nbins, acc,
+                     (const R *)coef, nell, half, nz, ny, zidx, yidx, (R)(H / unit), H, (R)scale, bin_of_s2, n_s2, nbins, acc,
                      (const cplx<R> *)tw);
 }
 
 void launch_ix(hipStream_t s, int prec, int N, const void *in, int rs, const FieldJob *jobs, int njobs,
-               const void *coef, int nell, int nz, int ny, const int *zidx, const int *yidx, double H, double unit,
+               const void *coef, int nell, int half, int nz, int ny, const int *zidx, const int *yidx, double H, double unit,
                double scale, const int *bin_of_s2, int64_t n_s2, int nbins, double *acc, const void *tw) {
   if (njobs <= 0 || nz <= 0 || ny <= 0 || nell > kMaxEll) return;
   if (prec == 0) {
-    PW_DISPATCH_N(ix_launch, float, s, in, rs, jobs, njobs, coef, nell, nz, ny, zidx, yidx, H, unit, scale,
+    PW_DISPATCH_N(ix_launch, float, s, in, rs, jobs, njobs, coef, nell, half, nz, ny, zidx, yidx, H, unit, scale,
                   bin_of_s2, n_s2, nbins, acc, tw)
   } else {
-    PW_DISPATCH_N(ix_launch, double, s, in, rs, jobs, njobs, coef, nell, nz, ny, zidx, yidx, H, unit, scale,
+    PW_DISPATCH_N(ix_launch, double, s, in, rs, jobs, njobs, coef, nell, half, nz, ny, zidx, yidx, H, unit, scale,
                   bin_of_s2, n_s2, nbins, acc, tw)
   }
 }

@@ -210,15 +210,10 @@ bool mid_reweight_generated(int lmax, int order, int all_parity);
 int mid_reweight_nfields(int lmax, int order, int all_parity);
 
 // ---- inverse path (inverse.hip) ----
-// Inverse z pass over full pencil-major spectra in[p][q * N + kz] (q = ky * nkx + kx):
-//   D != null: Z = conj(d_scale * D) * in / W(k)^2 (D is read before anything is written);
-//   fields p < n_inplace get Z written back in place and are not transformed;
-//   real_in: the input holds real values (imaginary part zero).
-// Other fields: inverse FFT along z, out[p - n_inplace][zrank[z]][ky * rs + kx] for retained z
-// (N * rs values per output plane).
-void launch_iz(hipStream_t s, int prec, int N, void *in, void *out, int nfields, int n_inplace,
-               int real_in, int64_t npen, int nkx, int rs, const void *D, double d_scale,
-               const void *winv, const int *zrank, int nz, const void *tw);
+// Bisector xi: inverse z pass of the real targets in[t][q * N + kz] (pencil-major), onto the planes
+// z = 0 .. nz - 1 <= N/2: out[t][z][q].
+void launch_iz(hipStream_t s, int prec, int N, const void *in, void *out, int nfields, int64_t npen, int nz,
+               const void *tw);
 // A sphere-pruned set on the device (Prune): row lengths and offsets, group offsets and slot counts
 struct SphereSet {
   const int *ycnt = nullptr;
@@ -234,12 +229,19 @@ struct SphereSet {
 void launch_fziz(hipStream_t s, int prec, int N, const void *in, void *prod, const SphereSet &sph, void *out,
                  int nfields, int n_inplace, int64_t npen, int rs, double d_scale, const void *winv, const int *zrank, int nz, const void *tw,
                  const int *planemask, ColTune tune = ColTune());
+// The same for xi with every product taken back to z, of which only the part even in D (odd_of[p] != 0:
+// odd) is needed: out[p][z][q] = the inverse z pass of Re (i Im) of the product, z = 0 .. nz - 1 <= N/2.
+// odd_of null: every field even.
+void launch_fziz_half(hipStream_t s, int prec, int N, const void *in, void *out, int nfields, int64_t npen, int rs,
+                      double d_scale, const void *winv, const int *odd_of, int nz, const void *tw,
+                      const int *planemask, ColTune tune = ColTune());
 // Inverse x pass (complex-to-real) of pair jobs on the rows (zr, yr) of in[p][zr][yr * rs + kx],
 // kx <= N/2, scaled by `scale`.
 //   X_l += coef[j][side][l] (|D| / unit)^alpha y_J^mu(D^) h, then FP64 r-binning of
-//   X_l into acc[l][b], acc[nell][b] (count), acc[nell + 1][b] (sum |D|).
+//   X_l into acc[l][b], acc[nell][b] (count), acc[nell + 1][b] (sum |D|).  half: the planes are
+//   z >= 0, each row off z = 0 and N/2 standing for its mirror too.
 void launch_ix(hipStream_t s, int prec, int N, const void *in, int rs,
-               const FieldJob *jobs, int njobs, const void *coef, int nell, int nz, int ny,
+               const FieldJob *jobs, int njobs, const void *coef, int nell, int half, int nz, int ny,
                const int *zidx, const int *yidx, double H, double unit, double scale, const int *bin_of_s2,
                int64_t n_s2, int nbins, double *acc, const void *tw);
 // Midpoint P real-space step (mix.hip): the y-pass output of the g fields in[p][z][y * rs + kx],

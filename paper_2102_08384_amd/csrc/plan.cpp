@@ -249,7 +249,7 @@ HostPlan build_host_plan(const pw_config &c) {
     for (int l : h.ells) h.ells_orders.push_back(o == 0 ? l : -1);
   h.check_extent = (h.path == PATH_MID_PK && c.order > 0 && c.ell_max > 0) ? 1 : 0;
   h.all_parity = (c.los == PW_MIDPOINT && c.midpoint_parity == PW_PARITY_ALL) ? 1 : 0;
-  h.n0 = 0; h.n_inv = 0; h.n_inplace = 0; h.nz = 0; h.ny = 0; h.n_targets = 0; h.n_a = 0;
+  h.n0 = 0; h.n_inv = 0; h.n_inplace = 0; h.nz = 0; h.ny = 0; h.half = 0; h.n_targets = 0; h.n_a = 0;
   const int N = h.N;
   const bool is_pk = c.stat == PW_PK;
 
@@ -359,22 +359,32 @@ HostPlan build_host_plan(const pw_config &c) {
     const int n = std::min(N, 2 * R + 1);
     h.nz = n;
     h.ny = n;
-    h.zrank.assign(N, -1);
-    h.zidx.assign(n, 0);
+    std::vector<int> yrank(N, -1);
+    h.yidx.assign(n, 0);
     for (int j = 0; j < n; ++j) {
       const int half = (n - 1) / 2;
       const int z = (n == N) ? j : (j <= half ? j : N - (n - j));
-      h.zidx[j] = z;
-      h.zrank[z] = j;
+      h.yidx[j] = z;
+      yrank[z] = j;
     }
-    h.yidx = h.zidx;
+    h.zidx = h.yidx;
+    h.zrank = yrank;
+    // xi: the planes z = 0 .. R alone.  (A last bin that rounds up to L/2 holds the cells at N/2 H on
+    // an axis, their own mirrors, where an odd weight does not cancel: the all-parity series then
+    // keeps every plane.)
+    h.half = (h.path != PATH_MID_PK && !(h.all_parity && 2 * R >= N)) ? 1 : 0;
+    if (h.half) {
+      h.nz = std::min(R, N / 2) + 1;
+      h.zidx.resize((size_t)h.nz);
+      for (int j = 0; j < h.nz; ++j) h.zidx[j] = j;
+    }
     const int nkx = h.fwd.nkx, rs = h.fwd.rs;
     h.iycnt.assign(N, 0);
     h.iyoff.assign(N, 0);
     for (int y = 0; y < N; ++y)
-      if (h.zrank[y] >= 0) {
+      if (yrank[y] >= 0) {
         h.iycnt[y] = nkx;
-        h.iyoff[y] = (int64_t)h.zrank[y] * rs;
+        h.iyoff[y] = (int64_t)yrank[y] * rs;
       }
   }
   if (h.path == PATH_MID_PK || h.path == PATH_MID_XI) {
@@ -387,6 +397,12 @@ HostPlan build_host_plan(const pw_config &c) {
       h.ijobs.push_back(k);
     }
   }
+  if (h.path == PATH_MID_XI && h.half && h.all_parity)
+    // field p's parity in D is that of J, so of alpha
+    for (const auto &kv : fields) {
+      h.odd_of.resize(fields.size(), 0);
+      h.odd_of[(size_t)kv.second] = std::get<0>(kv.first) & 1;
+    }
   if (h.path == PATH_BIS_XI) {
     // targets T_{l nu} at even_index(l, nu); pair jobs as for fields (alpha = 0)
     std::map<std::tuple<int, int, int>, int> tg;
@@ -508,7 +524,7 @@ size_t table_bytes(const HostPlan &h) {
              (h.fwd.moff.size() + h.sph.moff.size() + h.fwd.goff.size() + h.sph.goff.size() + h.fwd.yoff.size() +
               h.sph.yoff.size() + h.iyoff.size()) * 8 +
              (h.fwd.ycnt.size() + h.sph.ycnt.size() + h.fwd.gsize.size() + h.sph.gsize.size() + h.zrank.size() +
-              h.zidx.size() + h.yidx.size() + h.iycnt.size()) * 4;
+              h.zidx.size() + h.yidx.size() + h.iycnt.size() + h.odd_of.size()) * 4;
   b += (h.t_start.size() + h.t_sh.size() + h.t_ell.size() + h.t_p1.size() + h.t_p2.size()) * 4 +
        (h.t_coef.size() + h.winv.size() + h.icoef.size()) * rsz;
   b += (size_t)nt * nt * nt * 16 + (size_t)h.N * h.N * 8 + (size_t)h.N * 8;  // tile sort, occupancy

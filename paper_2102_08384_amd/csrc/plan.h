@@ -91,6 +91,8 @@ struct HostPlan {
   int n_inplace;             // fields kept in k-space by the inverse z pass (midpoint P)
   int nz, ny;                // retained z planes / y rows of the inverse outputs
   std::vector<int> zrank, zidx, yidx;   // index -> rank (-1: dropped) ; rank -> index
+  int half;                  // xi: the retained planes are z = 0 .. nz - 1 <= N/2, standing for +-z
+  std::vector<int> odd_of;   // half, all-parity: 1 for the fields odd in D
   std::vector<int> iycnt;    // per y index: nkx if retained else 0
   std::vector<int64_t> iyoff;  // per y index: rank * rs
   std::vector<FieldJob> ijobs;   // pair jobs of the inverse x pass (indices into the stack)
@@ -171,7 +173,7 @@ struct DevPlan {
   void *winv = nullptr;
   int *t_start = nullptr, *t_sh = nullptr, *t_ell = nullptr, *t_p1 = nullptr, *t_p2 = nullptr;
   void *t_coef = nullptr;
-  int *zrank = nullptr, *zidx = nullptr, *yidx = nullptr, *iycnt = nullptr;
+  int *zrank = nullptr, *zidx = nullptr, *yidx = nullptr, *iycnt = nullptr, *odd_of = nullptr;
   int64_t *iyoff = nullptr;
   void *icoef = nullptr;
   void *mesh = nullptr, *bufA = nullptr, *bufB = nullptr;
