@@ -823,8 +823,7 @@ void enqueue_paint(pw_ctx *ctx, Lane *ln, hipStream_t s, const DevPlan *dp, cons
   const HostPlan &h = *dp->host;
   const SortLayout SL = sort_layout(h.N, gal->n, ran->n);
   int *chunk_hist = (int *)((char *)records + records_bytes(h.prec, gal->n, ran->n));
-  launch_fill(s, dp->tile_counts, (size_t)dp->ntiles, 0);
-  launch_fill(s, dp->rowmask, (size_t)h.N * h.N, 0);
+  launch_clear3(s, dp->tile_counts, dp->ntiles, dp->rowmask, h.N * h.N, dp->planemask, h.N);
   launch_sort_count(s, SL, gx, gal->dtype, rx, ran->dtype, rnb, gal->n, ran->n, h.N, cfg->box_origin, h.H,
                     cfg->assign, chunk_hist, dp->tile_counts, dp->part_g, dp->part_r);
   const bool use_given = norm && norm->use_given;
@@ -835,8 +834,9 @@ void enqueue_paint(pw_ctx *ctx, Lane *ln, hipStream_t s, const DevPlan *dp, cons
   launch_sort_scatter(s, SL, gx, gal->dtype, rx, ran->dtype, gal->n, ran->n, h.prec, h.N, cfg->box_origin, h.H,
                       cfg->assign, dp->norm, chunk_hist, dp->tile_offsets, records);
   auto paint = [&](ColTune t) {
-    launch_tile_paint(s, h.prec, h.N, cfg->assign, dp->tile_offsets, dp->tile_slot, records, dp->norm,
-                      dp->tile_blocks, t);
+    // (buffer A is free until the x pass)
+    launch_tile_paint(s, h.prec, h.N, cfg->assign, gal->n + ran->n, dp->tile_offsets, dp->tile_slot, records, dp->norm,
+                      dp->tile_blocks, dp->bufA, spectrum_buffer_bytes(h), t);
   };
   auto gather = [&](ColTune t) {
     launch_tile_gather(s, h.prec, h.N, dp->tile_slot, dp->tile_blocks, dp->mesh, dp->rowmask, t);
@@ -1144,7 +1144,8 @@ DevPlan *launch_batch(pw_ctx *ctx, Lane &ln, const pw_config *cfg, int n, const 
   ba.n = n;
   for (int i = 0; i < n; ++i) {
     const DevPlan *p = plans[(size_t)i];
-    ba.s[i] = BatchSlot{p->mesh, p->bufA, p->bufB, p->rowlist, p->rowmask, p->zlist, p->planemask, p->norm, p->acc};
+    ba.s[i] = BatchSlot{p->mesh, p->bufA, p->bufB, p->rowlist, p->rowmask, p->zlist, p->planemask, p->norm, p->acc,
+                        p->out};
   }
   const int N = h.N;
   const Prune &F = h.fwd;
@@ -1163,14 +1164,12 @@ DevPlan *launch_batch(pw_ctx *ctx, Lane &ln, const pw_config *cfg, int n, const 
   }
   ln.res_rows = h.nell;
   const size_t nacc = (size_t)(h.nell + 2) * h.n_bins;
-  for (int i = 0; i < n; ++i) launch_fill(s, plans[(size_t)i]->acc, nacc, 1);
+  launch_clear_acc(s, (int)nacc, ba);
   if (!launch_contract_bis_generated(s, h.prec, h.ell_max, h.order / 2, dp0->bufA, F.nmodes, F.mstride,
                                      dp0->fwd.modecoord, N, dp0->bin_of_s2, (int64_t)h.bin_of_s2.size(), h.n_bins,
                                      h.kf, dp0->winv, dp0->acc, 0, &ba))
     fail(PW_EINVAL, "internal: no generated contraction for a batched launch");
-  for (int i = 0; i < n; ++i)
-    launch_finalize_pk(s, plans[(size_t)i]->acc, h.nell, h.n_bins, dp0->ells, plans[(size_t)i]->norm,
-                       plans[(size_t)i]->out);
+  launch_finalize_pk(s, dp0->acc, h.nell, h.n_bins, dp0->ells, dp0->norm, dp0->out, &ba);
   HIPCHECK(hipGetLastError());
   const size_t nres = (size_t)(h.nell + 2) * h.n_bins;
   const size_t slice = (nres * sizeof(double) + sizeof(DevNorm) + 255) & ~(size_t)255;

@@ -51,12 +51,14 @@ struct BatchSlot {
   void *A, *B;  // spectrum buffers: x- and z-pass output (A), y-pass output (B)
   const int *rowlist, *rowmask, *zlist, *planemask;
   const DevNorm *norm;
-  double *acc;
+  double *acc, *out;
 };
 struct Batch {
   int n;
   BatchSlot s[kMaxBatch];
 };
+// Zero the n accumulators of every catalog of a batch.
+void launch_clear_acc(hipStream_t s, int n, const Batch &ba);
 
 void upload_sh_const(const ShConst &c);
 void upload_sh_const_inverse(const ShConst &c);
@@ -69,6 +71,8 @@ void launch_finalize_norm(hipStream_t s, const double *pg, int nblk_g, const dou
                           double ga, double gI, double gS);
 // Zero n_elems values: prec 0 float, 1 double, 2 int.
 void launch_fill(hipStream_t s, void *p, size_t n_elems, int prec);
+// Zero three int arrays in one launch.
+void launch_clear3(hipStream_t s, int *a, int na, int *b, int nb, int *c, int nc);
 
 // Tile-binned painting: particles are counting-sorted by the tile of their anchor node
 // (nearest for TSC, lower for CIC); each occupied tile (+ one-node halo) is accumulated in
@@ -114,8 +118,11 @@ void launch_sort_scatter(hipStream_t s, const SortLayout &L, const void *gx, int
                          int assign, const DevNorm *norm, int *chunk_hist, const int *offsets, void *records);
 // blocks: scratch of ntiles * (TS+2)^3 values of the mesh precision, one block per occupied tile
 // (slot: [ntiles + 1] from the scan).
-void launch_tile_paint(hipStream_t s, int prec, int N, int assign, const int *offsets, const int *slot,
-                       const void *records, const DevNorm *norm, void *blocks, ColTune tune = ColTune());
+// scratch (free memory during the paint): the parts' blocks of tiles that several workgroups share;
+// n_part: the particles of both catalogs.
+void launch_tile_paint(hipStream_t s, int prec, int N, int assign, int64_t n_part, const int *offsets, const int *slot,
+                       const void *records, const DevNorm *norm, void *blocks, void *scratch, size_t scratch_bytes,
+                       ColTune tune = ColTune());
 // Every mesh node = the sum of the blocks covering it.  rowmask (N*N ints, zeroed by the
 // caller; may be null) receives 1 for every x-row (z, y) holding a non-zero node.
 void launch_tile_gather(hipStream_t s, int prec, int N, const int *slot, const void *blocks, void *mesh,
@@ -124,7 +131,7 @@ void launch_tile_gather(hipStream_t s, int prec, int N, const int *slot, const v
 // z-planes with a non-empty row, zlist = those planes in increasing order; counts into
 // norm->nrows_occ / nplanes_occ.  Every field of the forward transforms is the mesh times a
 // weight, so it vanishes exactly on empty rows.
-// blockcnt: occupancy_blocks(N) ints of scratch.
+// blockcnt: occupancy_blocks(N) ints of scratch.  The caller clears planemask.
 int occupancy_blocks(int N);
 void launch_occupancy(hipStream_t s, int N, const int *rowmask, int *rowlist, int *planemask, int *zlist,
                       int *blockcnt, DevNorm *norm);
@@ -194,7 +201,7 @@ void launch_contract_bis(hipStream_t s, int prec, int lmax, int bmax, const void
                          int64_t n_s2, int nbins, int nell, TermTable tab, double kf,
                          const void *winv, double *acc, ColTune tune = ColTune());
 void launch_finalize_pk(hipStream_t s, const double *acc, int nell, int nbins, const int *ells,
-                        const DevNorm *norm, double *out);
+                        const DevNorm *norm, double *out, const Batch *batch = nullptr);
 
 // Register-resident bisector contraction when its coupling is generated; false otherwise.
 // orders != 0: one accumulator row per (beta, l), rows beta * nell + l/2, then the mode count

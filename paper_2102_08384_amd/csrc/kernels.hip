@@ -783,7 +783,13 @@ void launch_contract_bis(hipStream_t s, int prec, int lmax, int bmax, const void
 
 // ------------------------------------------------------------------------------ finalize
 __global__ void k_finalize_pk(const double *acc, int nell, int nbins, const int *ells,
-                              const DevNorm *norm, double *out) {
+                              const DevNorm *norm, double *out, const Batch ba) {
+  if (ba.n) {  // catalog blockIdx.x of a batch
+    const BatchSlot &bs = ba.s[blockIdx.x];
+    acc = bs.acc;
+    norm = bs.norm;
+    out = bs.out;
+  }
   const double fourpi = 12.566370614359172953850573533118;
   const double I = norm->I, S = norm->S;
   for (int i = threadIdx.x; i < (nell + 1) * nbins; i += blockDim.x) {
@@ -801,8 +807,11 @@ __global__ void k_finalize_pk(const double *acc, int nell, int nbins, const int 
 }
 
 void launch_finalize_pk(hipStream_t s, const double *acc, int nell, int nbins, const int *ells,
-                        const DevNorm *norm, double *out) {
-  hipLaunchKernelGGL(k_finalize_pk, dim3(1), dim3(256), 0, s, acc, nell, nbins, ells, norm, out);
+                        const DevNorm *norm, double *out, const Batch *batch) {
+  Batch ba;
+  ba.n = 0;
+  if (batch) ba = *batch;
+  hipLaunchKernelGGL(k_finalize_pk, dim3(ba.n ? ba.n : 1), dim3(256), 0, s, acc, nell, nbins, ells, norm, out, ba);
 }
 
 }  // namespace pw
