@@ -19,7 +19,7 @@ BUILD_DIR = os.path.join(HERE, "_build")
 
 # mix.hip is built once per mesh size (its generated shapes compile side by side)
 MIX = [f"mix.hip@{n}" for n in (256, 512, 128, 64, 32, 16)]
-SOURCES = MIX + ["generated.hip", "kernels.hip", "inverse.hip", "paint.hip", "coeffs.cpp", "plan.cpp", "api.cpp"]
+SOURCES = MIX + ["nyq.hip", "generated.hip", "kernels.hip", "inverse.hip", "paint.hip", "coeffs.cpp", "plan.cpp", "api.cpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

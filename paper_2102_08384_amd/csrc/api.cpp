@@ -987,7 +987,6 @@ DevPlan *launch_estimate(pw_ctx *ctx, Lane &ln, const pw_config *cfg, const pw_c
     const double inv_n3 = 1.0 / ncell;
     const int npl = h.nz;  // retained z planes of the inverse outputs
     const double zpart = (double)h.n_inv * npl * F.npen_real * csz;
-    const double ypart = (double)h.n_inv * npl * h.ny * F.nkx * csz;
     const bool xi = h.path != PATH_MID_PK;
     if (xi) launch_fill(s, dp->acc, nacc, 1);
     void *zout;
@@ -1025,14 +1024,20 @@ DevPlan *launch_estimate(pw_ctx *ctx, Lane &ln, const pw_config *cfg, const pw_c
     }
     // inverse y pass of the retained z planes into B
     void *yout = B;
-    mark("iy", (double)h.n_inv * npl * N * F.nkx * csz + ypart);
+    const HalfLayout hl = half_layout(h);
+    const int nzr = h.mid_half ? N / 2 + 1 : npl;  // planes it leaves
+    const double yrows = (double)h.n_inv * nzr * h.ny * F.nkx * csz;
+    mark("iy", (double)h.n_inv * npl * N * F.nkx * csz + yrows);
     tuned_launch(ctx, ln, tune_key("iy", h, h.n_inv, npl, h.ny), fy_candidates(h.prec, h.n_inv), [&](ColTune t) {
-      launch_fy(s, h.prec, N, 1, zout, yout, h.n_inv, npl, F.nkx, F.rs, dp->iycnt, dp->iyoff,
-                (int64_t)h.ny * F.rs, dp->tw, nullptr, nullptr, nullptr, t);
+      if (h.mid_half)
+        launch_iy_half(s, h.prec, N, zout, yout, B + hl.nyx, B + hl.nyy, h.n_inv, F.nkx, F.rs, dp->odd_of, dp->tw, t);
+      else
+        launch_fy(s, h.prec, N, 1, zout, yout, h.n_inv, npl, F.nkx, F.rs, dp->iycnt, dp->iyoff,
+                  (int64_t)h.ny * F.rs, dp->tw, nullptr, nullptr, nullptr, t);
     });
     if (xi) {
       // a8: c2r along x fused with the |D|^alpha y(D^) weighting and FP64 r-binning
-      mark("ix_bin", ypart);
+      mark("ix_bin", yrows);
       launch_ix(s, h.prec, N, yout, F.rs, dp->ijobs, (int)h.ijobs.size(), dp->icoef, h.nell, h.half, h.nz, h.ny,
                 dp->zidx, dp->yidx, h.H, h.unit, inv_n3, dp->bin_of_s2, n_s2, h.n_bins, dp->acc, dp->tw);
       mark("finalize", 0.0);
@@ -1044,19 +1049,24 @@ DevPlan *launch_estimate(pw_ctx *ctx, Lane &ln, const pw_config *cfg, const pw_c
         // pass of A in one kernel, then A's y and z passes, pruned to the k-sphere of the bins
         // (ending in Aoff)
         const Prune &P = h.sph;
-        const double a1 = (double)h.n_a * N * N * P.nkx * csz, a2 = (double)h.n_a * N * P.npen * csz,
+        const double a1 = (double)h.n_a * nzr * N * P.nkx * csz, a2 = (double)h.n_a * nzr * P.npen * csz,
                      a3 = (double)h.n_a * P.nretained * rsz;
-        mark("mix", ypart + a1);
+        mark("mix", yrows + a1);
+        if (h.mid_half) {
+          launch_nyq_rows(s, h.prec, N, B + hl.nyy, B + hl.yx, h.n_inv, F.rs, dp->tw);
+          launch_nyq(s, h.prec, N, h.ell_max, h.order, h.all_parity, B + hl.nyx, B + hl.yx, B + hl.ax, B + hl.ay,
+                     inv_n3, h.H / h.unit);
+        }
         launch_mix(s, h.prec, N, h.ell_max, h.order, h.all_parity, yout, Aoff, F.rs, P.nkx, P.rs, inv_n3,
-                   h.H / h.unit, dp->tw);
+                   h.H / h.unit, dp->tw, B + hl.ax, B + hl.ay);
         mark("afy", a1 + a2);
         if (P.npen > 0)
-          launch_fy(s, h.prec, N, 0, Aoff, B, h.n_a, N, P.nkx, P.rs, dp->sph.ycnt, dp->sph.yoff, P.npen, dp->tw,
+          launch_fy(s, h.prec, N, 0, Aoff, B, h.n_a, nzr, P.nkx, P.rs, dp->sph.ycnt, dp->sph.yoff, P.npen, dp->tw,
                     nullptr, nullptr, nullptr);
         mark("afz", a2 + a3);
         if (P.npen > 0)
           launch_fz(s, h.prec, N, B, Aoff, h.n_a, P.npen, dp->sph.pinfo, dp->sph.moff, dp->sph.goff, dp->sph.gsize,
-                    P.mstride, dp->tw, nullptr, nullptr, ColTune(), nullptr, true);
+                    P.mstride, dp->tw, nullptr, nullptr, ColTune(), nullptr, true, h.mid_half != 0);
       }
       // a7 (midpoint): sum_nu y_l^nu(k^) Re[G_{l nu} + A_{l nu}] and FP64 k-binning
       mark("contract", (double)(h.n0 + h.n_a) * h.sph.nretained * rsz + 4.0 * h.sph.nretained);

@@ -8,6 +8,8 @@
 // MidReweight<L, K, ALLP, R> (midpoint; parity-even: Appendix D coefficients in the real basis,
 //   all-parity: Section 3.2's phi with the sign (-1)^J2 of g folded in):
 //   dirs(x, y, z, yD)   y_J1^mu1 of a unit vector at yD[J1*J1 + J1 + mu1], J1 <= K (parity-even: even J1)
+//   parity_part(yD, y2, other)  yD <- the part of J1's parity (other: the other part) of a function that
+//                       is yD at D and y2 at its mirror
 //   chunk<C>(g, yD, Dp, A)  A_{l nu} += sum_{alpha>0} sum Phi' y_J1^mu1(D^) |D|^alpha g_{alpha J2 mu2} over
 //   the g fields [kMixFields * C, kMixFields * (C + 1)) of the canonical order, g their values.
 //   The canonical order is (alpha, J, mu): alpha = 2, 4, .., K with J even <= L + alpha, or every
@@ -70,6 +72,14 @@ void emit_dirs(FILE *f, int K, bool all) {
         std::fprintf(f, "    yD[%d] = ((R)%.17g * q%d_%d) * c%d; yD[%d] = ((R)%.17g * q%d_%d) * s%d;\n", J * J + J + m,
                      nrm, J, m, m, J * J + J - m, nrm, J, m, m);
     }
+  std::fprintf(f, "  }\n");
+  std::fprintf(f, "  __device__ __forceinline__ static void parity_part(R *yD, const R *y2, bool other) {\n"
+                  "    const R e = other ? (R)-0.5 : (R)0.5;\n");
+  if (all) std::fprintf(f, "    const R o = -e;\n");
+  for (int J = 0; J <= K; J += all ? 1 : 2)
+    for (int m = -J; m <= J; ++m)
+      std::fprintf(f, "    yD[%d] = (R)0.5 * yD[%d] + %s * y2[%d];\n", J * J + J + m, J * J + J + m, (J & 1) ? "o" : "e",
+                   J * J + J + m);
   std::fprintf(f, "  }\n");
 }
 

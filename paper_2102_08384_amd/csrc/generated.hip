@@ -237,7 +237,7 @@ void launch_targets(hipStream_t s, int prec, int N, int lmax, int bmax, const vo
 // ------------------------------------------------------------------------------ mix (by mesh size)
 #define PW_MIX_ARGS                                                                                \
   hipStream_t s, int prec, int lmax, int order, int all_parity, const void *in, void *out, int rs, \
-      int nkx, int rso, double scale, double Hu, const void *tw
+      int nkx, int rso, double scale, double Hu, const void *tw, const void *ax, const void *ay
 void launch_mix_16(PW_MIX_ARGS);
 void launch_mix_32(PW_MIX_ARGS);
 void launch_mix_64(PW_MIX_ARGS);
@@ -246,10 +246,10 @@ void launch_mix_256(PW_MIX_ARGS);
 void launch_mix_512(PW_MIX_ARGS);
 
 void launch_mix(hipStream_t s, int prec, int N, int lmax, int order, int all_parity, const void *in, void *out, int rs,
-                int nkx, int rso, double scale, double Hu, const void *tw) {
+                int nkx, int rso, double scale, double Hu, const void *tw, const void *ax, const void *ay) {
   switch (N) {
 #define PW_MIX_CASE(n) \
-  case n: launch_mix_##n(s, prec, lmax, order, all_parity, in, out, rs, nkx, rso, scale, Hu, tw); break;
+  case n: launch_mix_##n(s, prec, lmax, order, all_parity, in, out, rs, nkx, rso, scale, Hu, tw, ax, ay); break;
     PW_MIX_CASE(16) PW_MIX_CASE(32) PW_MIX_CASE(64) PW_MIX_CASE(128) PW_MIX_CASE(256) PW_MIX_CASE(512)
 #undef PW_MIX_CASE
     default: break;

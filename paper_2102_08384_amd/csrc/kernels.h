@@ -171,12 +171,14 @@ void launch_fy(hipStream_t s, int prec, int N, int inv, const void *in, void *ou
 // (C = 128 bytes / complex size, the pencils per workgroup).  Field stride mstride.
 // planemask (may be null): empty z-planes of the input are read as zeros.
 // fmap (may be null): the output field index of each input field p (sphere-pruned sets only)
-// real_only (sphere-pruned sets only): the real parts alone are stored, as reals in the same layout
+// real_only (sphere-pruned sets only): the real parts alone are stored, as reals in the same layout;
+// with `half` besides, the input holds the planes z = 0 .. N/2 of a field that is even in D, and plane -z
+// is the complex conjugate of plane z
 void launch_fz(hipStream_t s, int prec, int N, const void *in, void *out, int nfields,
                int64_t npen, const PencilInfo *pinfo, const int64_t *moff, const int64_t *goff,
                const int *gsize, int64_t mstride, const void *tw, const int *planemask,
                const int *fmap = nullptr, ColTune tune = ColTune(), const Batch *batch = nullptr,
-               bool real_only = false);
+               bool real_only = false, bool half = false);
 
 // Bisector contraction + FP64 k-binning.
 struct TermTable {
@@ -251,13 +253,30 @@ void launch_ix(hipStream_t s, int prec, int N, const void *in, int rs,
                const FieldJob *jobs, int njobs, const void *coef, int nell, int half, int nz, int ny,
                const int *zidx, const int *yidx, double H, double unit, double scale, const int *bin_of_s2,
                int64_t n_s2, int nbins, double *acc, const void *tw);
+// Midpoint P from the half z = 0 .. N/2 of the separations (k_iy_half has the reasons): the inverse y
+// pass of in[p][z][y * rs + kx], every z, into out[p][z <= N/2][y * rs + kx] (the part of g of the parity
+// odd_of[p]; null: even), and the other part on the planes y = N/2 (nyy[p][z][kx]) and x = N/2
+// (nyx[p][z][y], real, transformed along y).
+void launch_iy_half(hipStream_t s, int prec, int N, const void *in, void *out, void *nyx, void *nyy, int nfields,
+                    int nkx, int rs, const int *odd_of, const void *tw, ColTune tune = ColTune());
+// nyy to real space: yx[p][z][x].
+void launch_nyq_rows(hipStream_t s, int prec, int N, const void *nyy, void *yx, int nfields, int rs, const void *tw);
+// The contributions of these planes to the A fields, A[i][z][.]: ax over y at x = N/2 (zero at y = N/2),
+// ay over x at y = N/2.
+void launch_nyq(hipStream_t s, int prec, int N, int lmax, int order, int all_parity, const void *nyx, const void *yx,
+                void *ax, void *ay, double scale, double Hu);
 // Midpoint P real-space step (mix.hip): the y-pass output of the g fields in[p][z][y * rs + kx],
 // kx <= N/2, through the inverse x pass (scaled by `scale`), the generated re-weighting
 // A_{l nu}(D) with |D| in the length unit of the forward weights (Hu = H / unit), and the forward x
 // pass of the A fields, out[i][z][y * rso + kx], kx < nkx.  prec, N and (lmax, order, all_parity)
-// select a built shape (mid_reweight_generated).
+// select a built shape (mid_reweight_generated).  From kMidHalfMesh on the planes are z = 0 .. N/2, and
+// ax / ay are added (launch_nyq); below it every z, ax and ay unused.
 void launch_mix(hipStream_t s, int prec, int N, int lmax, int order, int all_parity, const void *in, void *out, int rs,
-                int nkx, int rso, double scale, double Hu, const void *tw);
+                int nkx, int rso, double scale, double Hu, const void *tw, const void *ax, const void *ay);
+// Smallest mesh whose midpoint P_l works on half of the separations: at 64^3 the two more launches cost
+// about what the halves save (whole estimates: 15 g fields 290.2 -> 290.6 us, 73 419 -> 406 us, 130
+// 564 -> 541 us), at 128^3 they gain 7 to 20%; smaller meshes are launch-bound throughout.
+constexpr int kMidHalfMesh = 64;
 // Bisector xi targets: T[t][i] = sum S Re(conj(R_p1) R_p2) / W(k)^2 over the full
 // pencil-major spectra (i = q * N + kz, q = ky * rs + kx), written as real values (generated).
 // Field p of spec starts at p * mstride; target t of T at t * nmodes.

@@ -504,7 +504,7 @@ __global__ void __launch_bounds__((ColShape<R, N>::THREADS))
 k_fz(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, int nfields, int fpb, int64_t npen,
      const PencilInfo *__restrict__ pinfo, const int64_t *__restrict__ moff, const int64_t *__restrict__ goff,
      const int *__restrict__ gsize, int64_t mstride, const cplx<R> *__restrict__ tw,
-     const int *__restrict__ planemask, const int *__restrict__ fmap, const Batch ba) {
+     const int *__restrict__ planemask, const int *__restrict__ fmap, int half, const Batch ba) {
   constexpr int T = ColShape<R, N>::T, C = ColShape<R, N>::C, NT = ColShape<R, N>::THREADS;
   if (ba.n) {  // catalog blockIdx.z of a batch
     const BatchSlot &bs = ba.s[blockIdx.z];
@@ -545,6 +545,18 @@ k_fz(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, int nfields, int
     if (S == 0) return;  // no pencil of the group holds a mode (uniform, after the last barrier)
   }
   auto load = [&](int p, cplx<R> *v) {
+    if constexpr (REAL_ONLY) {
+      if (half) {  // (the imaginary parts of the planes 0 and N/2 only reach the dropped part)
+        const cplx<R> *src = in + (size_t)p * (N / 2 + 1) * npen;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+          const int z = t + s * T, zh = z > N / 2 ? N - z : z;
+          v[s] = has ? src[(size_t)zh * npen + q] : mk<R>(0, 0);
+          if (z > N / 2) v[s].y = -v[s].y;
+        }
+        return;
+      }
+    }
     const cplx<R> *src = in + (size_t)p * N * npen;
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
@@ -603,7 +615,7 @@ template <typename R, int N>
 static void fz_launch(hipStream_t s, const void *in, void *out, int nfields, int64_t npen,
                       const PencilInfo *pinfo, const int64_t *moff, const int64_t *goff, const int *gsize,
                       int64_t mstride, const void *tw, const int *planemask, const int *fmap,
-                      ColTune tune, const Batch *batch, bool real_only) {
+                      ColTune tune, const Batch *batch, bool real_only, bool half) {
   constexpr int C = ColShape<R, N>::C;
   static_assert(C == 128 / (int)sizeof(cplx<R>), "z-pass groups must match 128-byte slot rows");
   const unsigned ng = (unsigned)((npen + C - 1) / C);
@@ -621,28 +633,28 @@ static void fz_launch(hipStream_t s, const void *in, void *out, int nfields, int
   if (goff && real_only)
     hipLaunchKernelGGL((k_fz<R, N, true, true>), grid, dim3(ColShape<R, N>::THREADS), 0, s, (const cplx<R> *)in,
                        (cplx<R> *)out, nfields, fpb, npen, pinfo, moff, goff, gsize, mstride, (const cplx<R> *)tw,
-                       planemask, fmap, ba);
+                       planemask, fmap, half, ba);
   else if (goff)
     hipLaunchKernelGGL((k_fz<R, N, true, false>), grid, dim3(ColShape<R, N>::THREADS), 0, s, (const cplx<R> *)in,
                        (cplx<R> *)out, nfields, fpb, npen, pinfo, moff, goff, gsize, mstride, (const cplx<R> *)tw,
-                       planemask, fmap, ba);
+                       planemask, fmap, half, ba);
   else
     hipLaunchKernelGGL((k_fz<R, N, false, false>), grid, dim3(ColShape<R, N>::THREADS), 0, s, (const cplx<R> *)in,
                        (cplx<R> *)out, nfields, fpb, npen, pinfo, moff, goff, gsize, mstride, (const cplx<R> *)tw,
-                       planemask, (const int *)nullptr, ba);
+                       planemask, (const int *)nullptr, 0, ba);
 }
 
 void launch_fz(hipStream_t s, int prec, int N, const void *in, void *out, int nfields, int64_t npen,
                const PencilInfo *pinfo, const int64_t *moff, const int64_t *goff, const int *gsize,
                int64_t mstride, const void *tw, const int *planemask, const int *fmap, ColTune tune,
-               const Batch *batch, bool real_only) {
+               const Batch *batch, bool real_only, bool half) {
   if (nfields <= 0 || npen <= 0) return;
   if (prec == 0) {
     PW_DISPATCH_N(fz_launch, float, s, in, out, nfields, npen, pinfo, moff, goff, gsize, mstride, tw, planemask,
-                  fmap, tune, batch, real_only)
+                  fmap, tune, batch, real_only, half)
   } else {
     PW_DISPATCH_N(fz_launch, double, s, in, out, nfields, npen, pinfo, moff, goff, gsize, mstride, tw, planemask,
-                  fmap, tune, batch, real_only)
+                  fmap, tune, batch, real_only, half)
   }
 }
 

@@ -31,7 +31,8 @@ template <int L, int K, bool ALLP, typename R> struct MidReweight {
 // time of VALU work (the transforms and the generated terms).  As three passes (inverse x to real
 // g fields, re-weighting, forward x of A) the g fields were written and read again.  Measured, FP32,
 // ell_max 4, order 4, three passes -> this one: 256^3 3.76 -> 1.48 ms (all-parity, 130 g fields:
-// 6.24 -> 2.65 ms), 512^3 26.5 -> 13.8 ms.
+// 6.24 -> 2.65 ms), 512^3 26.5 -> 13.8 ms; on the half z >= 0 of the rows, with the two kernels of
+// nyq.hip: 0.80 (1.38) and 7.1 ms.
 //
 // Exchange swizzle: element i of a pair's N complex values sits at i ^ ((i >> 5) & 7) ^
 // (((i >> 6) & 3) << 3): the radix-8 stages' stores (strides 8 and 64 / N) and the reads (stride
@@ -52,7 +53,7 @@ template <typename R, int N, int L, int K, bool ALLP>
 __global__ void __launch_bounds__((MixShape<R, N>::NT))
 __attribute__((amdgpu_waves_per_eu((MixShape<R, N>::template waves<K, ALLP>()), 8)))
 k_mix(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, int rs, int nkx, int rso, R scale, R Hu,
-      const cplx<R> *__restrict__ tw) {
+      const cplx<R> *__restrict__ tw, const R *__restrict__ ax, const R *__restrict__ ay) {
   typedef MixShape<R, N> S;
   constexpr int T = S::T, F = kMixFields;
   using MR = MidReweight<L, K, ALLP, R>;
@@ -62,7 +63,9 @@ k_mix(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, int rs, int nkx
   const int t = tid & (T - 1), grp = tid / T, j = grp & 7, rl = grp >> 3;  // pair j of row rl
   const int partner = (tid & 63 & ~(T - 1)) | ((T - t) & (T - 1));         // lane T - t of the group
   const size_t row = (size_t)blockIdx.x * S::ROWS + rl;                    // z * N + y
-  const size_t fin = (size_t)N * N * rs, fout = (size_t)N * N * rso;
+  constexpr bool HALF = N >= kMidHalfMesh;  // rows z = 0 .. N/2 (see k_iy_half), else every z
+  constexpr int NZ = HALF ? N / 2 + 1 : N;
+  const size_t fin = (size_t)NZ * N * rs, fout = (size_t)NZ * N * rso;
   FftTw<R, N> twr;
   twr.load(t, tw);
   int buf = 0;
@@ -104,6 +107,12 @@ k_mix(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, int rs, int nkx
     // D = 0: |D|^alpha = 0 for every alpha > 0, so the direction is immaterial
     const R ir = d2 > (R)0 ? (R)1 / sqrt(d2) : (R)0;
     MR::dirs(dx * ir, dy * ir, d2 > (R)0 ? dz * ir : (R)1, yD);
+    if (HALF && z > 0 && z < N / 2 && (x == N / 2 || y == N / 2)) {
+      // the mirrored index stands for (sx, ..) where x = N/2: the part of y_J1 of J1's parity
+      R y2[(K + 1) * (K + 1)];
+      MR::dirs(x == N / 2 ? dx * ir : -dx * ir, y == N / 2 ? dy * ir : -dy * ir, -dz * ir, y2);
+      MR::parity_part(yD, y2, false);
+    }
   }
 #pragma unroll
   for (int i = 0; i < NA; ++i) A[i] = 0;
@@ -153,6 +162,14 @@ k_mix(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, int rs, int nkx
     buf ^= 1;  // (the next step's transforms write the other buffer; its barrier covers these reads)
   };
   for_each_const<NCH>(step);
+  if (HALF) {  // the other parts on the planes x = N/2 and y = N/2
+    const int y = (int)(crow & (N - 1)), z = (int)(crow / N);
+    if (z > 0 && z < N / 2 && (x == N / 2 || y == N / 2)) {
+      const R *src = y == N / 2 ? ay + (size_t)z * N + x : ax + (size_t)z * N + y;
+#pragma unroll
+      for (int i = 0; i < NA; ++i) A[i] += src[(size_t)i * NZ * N];
+    }
+  }
 
   // forward transforms of the A rows, kMixFields rows at a time
   for_each_const<(NA + F - 1) / F>([&](auto ic) {
@@ -200,20 +217,22 @@ k_mix(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, int rs, int nkx
 
 template <typename R, int N, int L, int K, bool ALLP>
 static void mix_launch(hipStream_t s, const void *in, void *out, int rs, int nkx, int rso, double scale, double Hu,
-                       const void *tw) {
+                       const void *tw, const void *ax, const void *ay) {
   typedef MixShape<R, N> S;
-  hipLaunchKernelGGL((k_mix<R, N, L, K, ALLP>), dim3((unsigned)((size_t)N * N / S::ROWS)), dim3(S::NT), 0, s,
-                     (const cplx<R> *)in, (cplx<R> *)out, rs, nkx, rso, (R)scale, (R)Hu, (const cplx<R> *)tw);
+  hipLaunchKernelGGL((k_mix<R, N, L, K, ALLP>), dim3((unsigned)((N >= kMidHalfMesh ? N / 2 + 1 : N) * N / S::ROWS)), dim3(S::NT), 0, s,
+                     (const cplx<R> *)in, (cplx<R> *)out, rs, nkx, rso, (R)scale, (R)Hu, (const cplx<R> *)tw,
+                     (const R *)ax, (const R *)ay);
 }
 
 #define PW_CAT2(a, b) a##b
 #define PW_CAT(a, b) PW_CAT2(a, b)
 void PW_CAT(launch_mix_, PW_MIX_N)(hipStream_t s, int prec, int lmax, int order, int all_parity, const void *in,
-                                   void *out, int rs, int nkx, int rso, double scale, double Hu, const void *tw) {
+                                   void *out, int rs, int nkx, int rso, double scale, double Hu, const void *tw,
+                                   const void *ax, const void *ay) {
 #define PW_MX(L, K, AP)                                                                          \
   if (lmax == L && order == K && (all_parity != 0) == AP) {                                      \
-    if (prec == 0) mix_launch<float, PW_MIX_N, L, K, AP>(s, in, out, rs, nkx, rso, scale, Hu, tw);          \
-    else mix_launch<double, PW_MIX_N, L, K, AP>(s, in, out, rs, nkx, rso, scale, Hu, tw);                   \
+    if (prec == 0) mix_launch<float, PW_MIX_N, L, K, AP>(s, in, out, rs, nkx, rso, scale, Hu, tw, ax, ay);  \
+    else mix_launch<double, PW_MIX_N, L, K, AP>(s, in, out, rs, nkx, rso, scale, Hu, tw, ax, ay);           \
     return;                                                                                      \
   }
   PW_MIX_SHAPES(PW_MX)

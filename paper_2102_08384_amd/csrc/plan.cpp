@@ -249,7 +249,7 @@ HostPlan build_host_plan(const pw_config &c) {
     for (int l : h.ells) h.ells_orders.push_back(o == 0 ? l : -1);
   h.check_extent = (h.path == PATH_MID_PK && c.order > 0 && c.ell_max > 0) ? 1 : 0;
   h.all_parity = (c.los == PW_MIDPOINT && c.midpoint_parity == PW_PARITY_ALL) ? 1 : 0;
-  h.n0 = 0; h.n_inv = 0; h.n_inplace = 0; h.nz = 0; h.ny = 0; h.half = 0; h.n_targets = 0; h.n_a = 0;
+  h.n0 = 0; h.n_inv = 0; h.n_inplace = 0; h.nz = 0; h.ny = 0; h.half = 0; h.mid_half = 0; h.n_targets = 0; h.n_a = 0;
   const int N = h.N;
   const bool is_pk = c.stat == PW_PK;
 
@@ -397,11 +397,12 @@ HostPlan build_host_plan(const pw_config &c) {
       h.ijobs.push_back(k);
     }
   }
-  if (h.path == PATH_MID_XI && h.half && h.all_parity)
-    // field p's parity in D is that of J, so of alpha
+  h.mid_half = (h.path == PATH_MID_PK && h.n_inv > 0 && N >= kMidHalfMesh) ? 1 : 0;
+  if (h.all_parity && (h.half || h.mid_half))
+    // a field's parity in D is that of J, so of alpha
     for (const auto &kv : fields) {
-      h.odd_of.resize(fields.size(), 0);
-      h.odd_of[(size_t)kv.second] = std::get<0>(kv.first) & 1;
+      h.odd_of.resize((size_t)h.n_inv, 0);
+      if (kv.second >= h.n_inplace) h.odd_of[(size_t)(kv.second - h.n_inplace)] = std::get<0>(kv.first) & 1;
     }
   if (h.path == PATH_BIS_XI) {
     // targets T_{l nu} at even_index(l, nu); pair jobs as for fields (alpha = 0)
@@ -476,10 +477,24 @@ HostPlan build_host_plan(const pw_config &c) {
     // planes and the A fields' x-pass and z-pass outputs; B holds the y-pass outputs
     const size_t sb = spectrum_buffer_bytes(h), front = front_bytes(h), avail = sb > front ? sb - front : 0;
     if ((size_t)h.n_inv * h.nz * h.fwd.npen * csz > avail || (size_t)h.n_a * N * N * h.sph.rs * csz > avail ||
-        (size_t)h.n_a * h.sph.mstride * csz > avail)
+        (size_t)h.n_a * h.sph.mstride * csz > avail || half_layout(h).total > sb)
       plan_fail(PW_EINVAL, "internal: A fields do not fit the spectrum buffer");
   }
   return h;
+}
+
+HalfLayout half_layout(const HostPlan &h) {
+  HalfLayout l;
+  if (!h.mid_half) return l;
+  const size_t rsz = h.prec == PW_FP32 ? 4 : 8, nz = (size_t)h.N / 2 + 1;
+  auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
+  l.nyy = up((size_t)h.n_inv * nz * h.N * h.fwd.rs * 2 * rsz);
+  l.nyx = l.nyy + up((size_t)h.n_inv * nz * h.fwd.rs * 2 * rsz);
+  l.yx = l.nyx + up((size_t)h.n_inv * nz * h.N * rsz);
+  l.ax = l.yx + up((size_t)h.n_inv * nz * h.N * rsz);
+  l.ay = l.ax + up((size_t)h.n_a * nz * h.N * rsz);
+  l.total = l.ay + up((size_t)h.n_a * nz * h.N * rsz);
+  return l;
 }
 
 size_t front_bytes(const HostPlan &h) {

@@ -92,7 +92,8 @@ struct HostPlan {
   int nz, ny;                // retained z planes / y rows of the inverse outputs
   std::vector<int> zrank, zidx, yidx;   // index -> rank (-1: dropped) ; rank -> index
   int half;                  // xi: the retained planes are z = 0 .. nz - 1 <= N/2, standing for +-z
-  std::vector<int> odd_of;   // half, all-parity: 1 for the fields odd in D
+  int mid_half;              // midpoint P: real space on the planes z = 0 .. N/2 (launch_iy_half)
+  std::vector<int> odd_of;   // (mid_)half, all-parity: [n_inv] 1 for the fields odd in D
   std::vector<int> iycnt;    // per y index: nkx if retained else 0
   std::vector<int64_t> iyoff;  // per y index: rank * rs
   std::vector<FieldJob> ijobs;   // pair jobs of the inverse x pass (indices into the stack)
@@ -143,6 +144,11 @@ size_t catalog_bytes(const pw_config &c, const pw_catalog &gal, const pw_catalog
 size_t records_bytes(int prec, int64_t n_gal, int64_t n_ran);
 // bytes of each of the two spectrum buffers (memory-lean: of the k-sphere buffer)
 size_t spectrum_buffer_bytes(const HostPlan &h);
+// midpoint P_l on half of the separations: byte offsets into buffer B, behind the half planes
+struct HalfLayout {
+  size_t nyy = 0, nyx = 0, yx = 0, ax = 0, ay = 0, total = 0;
+};
+HalfLayout half_layout(const HostPlan &h);
 // midpoint P_l: the alpha = 0 products at the front of buffer A
 size_t front_bytes(const HostPlan &h);
 // memory-lean bisector: x-pass and y-pass work buffers of one field group
