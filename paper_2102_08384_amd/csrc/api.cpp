@@ -479,7 +479,6 @@ std::unique_ptr<DevPlan> build_dev_plan(pw_ctx *ctx, const pw_config *cfg, char 
       d.ycnt = upload(M, p.ycnt);
       d.yoff = upload(M, p.yoff);
       d.pinfo = upload(M, p.pinfo);
-      d.moff = upload(M, p.moff);
       d.modecoord = upload(M, p.modecoord);
       d.goff = upload(M, p.goff);
       d.gsize = upload(M, p.gsize);
@@ -920,7 +919,7 @@ DevPlan *launch_estimate(pw_ctx *ctx, Lane &ln, const pw_config *cfg, const pw_c
       });
       launch_fy(s, h.prec, N, 0, B, dp->bufC, nf, N, F.nkx, F.rs, dp->fwd.ycnt, dp->fwd.yoff, F.npen, dp->tw,
                 dp->rowmask, dp->zlist, dp->norm);
-      launch_fz(s, h.prec, N, dp->bufC, A, nf, F.npen, dp->fwd.pinfo, dp->fwd.moff, dp->fwd.goff, dp->fwd.gsize,
+      launch_fz(s, h.prec, N, dp->bufC, A, nf, F.npen, dp->fwd.pinfo, dp->fwd.goff, dp->fwd.gsize,
                 F.mstride, dp->tw, dp->planemask, dp->lean_fmap + f0);
     }
   } else {
@@ -943,7 +942,7 @@ DevPlan *launch_estimate(pw_ctx *ctx, Lane &ln, const pw_config *cfg, const pw_c
       if (F.npen > 0)
         tuned_launch(ctx, ln, tune_key("fz", h, h.nfields, F.npen, F.goff.empty() ? 0 : 1),
                      fz_candidates(h.nfields), [&](ColTune t) {
-                       launch_fz(s, h.prec, N, B, A, h.nfields, F.npen, dp->fwd.pinfo, dp->fwd.moff, dp->fwd.goff,
+                       launch_fz(s, h.prec, N, B, A, h.nfields, F.npen, dp->fwd.pinfo, dp->fwd.goff,
                                  dp->fwd.gsize, F.mstride, dp->tw, dp->planemask, nullptr, t);
                      });
     }
@@ -1065,7 +1064,7 @@ DevPlan *launch_estimate(pw_ctx *ctx, Lane &ln, const pw_config *cfg, const pw_c
                     nullptr, nullptr, nullptr);
         mark("afz", a2 + a3);
         if (P.npen > 0)
-          launch_fz(s, h.prec, N, B, Aoff, h.n_a, P.npen, dp->sph.pinfo, dp->sph.moff, dp->sph.goff, dp->sph.gsize,
+          launch_fz(s, h.prec, N, B, Aoff, h.n_a, P.npen, dp->sph.pinfo, dp->sph.goff, dp->sph.gsize,
                     P.mstride, dp->tw, nullptr, nullptr, ColTune(), nullptr, true, h.mid_half != 0);
       }
       // a7 (midpoint): sum_nu y_l^nu(k^) Re[G_{l nu} + A_{l nu}] and FP64 k-binning
@@ -1166,7 +1165,7 @@ DevPlan *launch_batch(pw_ctx *ctx, Lane &ln, const pw_config *cfg, int n, const 
     launch_fy(s, h.prec, N, 0, dp0->bufA, dp0->bufB, h.nfields, N, F.nkx, F.rs, dp0->fwd.ycnt, dp0->fwd.yoff,
               F.npen, dp0->tw, dp0->rowmask, dp0->zlist, dp0->norm,
               tuned_choice(ctx, tune_key("fy", h, h.nfields, F.nkx, F.npen), fy_candidates(h.prec, h.nfields)), &ba);
-    launch_fz(s, h.prec, N, dp0->bufB, dp0->bufA, h.nfields, F.npen, dp0->fwd.pinfo, dp0->fwd.moff, dp0->fwd.goff,
+    launch_fz(s, h.prec, N, dp0->bufB, dp0->bufA, h.nfields, F.npen, dp0->fwd.pinfo, dp0->fwd.goff,
               dp0->fwd.gsize, F.mstride, dp0->tw, dp0->planemask, nullptr,
               tuned_choice(ctx, tune_key("fz", h, h.nfields, F.npen, F.goff.empty() ? 0 : 1),
                            fz_candidates(h.nfields)),

@@ -176,7 +176,7 @@ bool mid_reweight_generated(int lmax, int order, int all_parity) {
   return mid_reweight_nfields(lmax, order, all_parity) >= 0;
 }
 
-// Bisector xi targets over the full pencil-major spectra: one thread per mode.
+// Bisector xi targets over the full spectra: one thread per mode.
 template <typename R, int LMAX, int BMAX>
 __global__ void __launch_bounds__(256)
 k_targets(const cplx<R> *__restrict__ spec, int64_t nmodes, int64_t mstride, int N, int rs,
@@ -194,8 +194,10 @@ k_targets(const cplx<R> *__restrict__ spec, int64_t nmodes, int64_t mstride, int
     CT::targets(a, full);
     R iw2 = (R)1;
     if (winv) {
-      const int64_t q = i / N;
-      const int kz = (int)(i - q * N), ky = (int)(q / rs), kx = (int)(q - (int64_t)ky * rs);
+      // mode i = (g N + kz) C + c of pencil q = g C + c
+      constexpr int C = 128 / (int)sizeof(cplx<R>);
+      const int64_t row = i / C, g = row / N, q = g * C + (i - row * C);
+      const int kz = (int)(row - g * N), ky = (int)(q / rs), kx = (int)(q - (int64_t)ky * rs);
       const R iw = winv[kx] * winv[ky] * winv[kz];
       iw2 = iw * iw;
     }

@@ -1,7 +1,7 @@
 // HIP kernels of the inverse-transform paths (gfx950, wave64).
 //
-//   iz             bisector xi_l: inverse FFT along z of the real targets, pencil-major, two to a
-//                  transform; output pruned to the retained planes z >= 0
+//   iz             bisector xi_l: inverse FFT along z of the real targets, two to a transform;
+//                  output pruned to the retained planes z >= 0
 //   fziz           midpoint g fields: forward FFT along z, the product conj(D) Q / W^2
 //                  (Section 3.2) and the inverse FFT along z in one pass over each pencil
 //   fziz_half      the same for xi_l, whose sums need only the part of g that is even (or odd) in D:
@@ -67,51 +67,38 @@ template <typename R, int N>
 __global__ void __launch_bounds__((ColShape<R, N>::THREADS))
 k_iz(const R *__restrict__ in, cplx<R> *__restrict__ out, int nfields, int64_t npen, int nz,
      const cplx<R> *__restrict__ tw) {
-  constexpr int T = ColShape<R, N>::T, C = ColShape<R, N>::C, NT = ColShape<R, N>::THREADS;
-  constexpr int LOGN = log2i(N);
+  constexpr int T = ColShape<R, N>::T, C = ColShape<R, N>::C;
   __shared__ cplx<R> lds[N * (C + 1)];
   const int c = threadIdx.x % C, t = threadIdx.x / C;
-  const int64_t q0 = (int64_t)blockIdx.x * C;
-  const int64_t q = q0 + c;
-  const int64_t left = npen - q0;
-  const int nval = (int)((left < C ? left : C) * N);  // valid values of this block's chunk
+  const int64_t q = (int64_t)blockIdx.x * C + c;
   auto at = [c](int i) -> cplx<R> & { return lds[i * (C + 1) + c]; };
   auto sync = []() { __syncthreads(); };
   FftTw<R, N> twr;
   twr.load(t, tw);
   wait_vmem();
+  // the pair's values of this lane, the next pair's loaded while the current one is transformed
+  // (npen is a multiple of C: every pencil of the group exists)
+  R xa[8], xb[8];
+  const R *mine = in + (size_t)blockIdx.x * N * C + t * C + c;
   const size_t fstride = (size_t)npen * N;
-  // the pair's chunks (pencils q0 .. q0 + C - 1, contiguous: element e = cc * N + kz): PER values per
-  // thread, the next pair's loaded while the current one is transformed
-  constexpr int PER = C * N / NT;
-  R xa[PER], xb[PER];
   auto fetch = [&](int p) {
-    const R *src = in + (size_t)p * fstride + (size_t)q0 * N;
+    const R *src = mine + (size_t)p * fstride;
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int e = threadIdx.x + k * NT;
-      xa[k] = e < nval ? __builtin_nontemporal_load(src + e) : (R)0;
-      xb[k] = (e < nval && p + 1 < nfields) ? __builtin_nontemporal_load(src + fstride + e) : (R)0;
+    for (int s = 0; s < 8; ++s) {
+      xa[s] = __builtin_nontemporal_load(src + s * T * C);
+      xb[s] = p + 1 < nfields ? __builtin_nontemporal_load(src + fstride + s * T * C) : (R)0;
     }
   };
   fetch(0);
   for (int p = 0; p < nfields; p += 2) {
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int e = threadIdx.x + k * NT;
-      lds[(e & (N - 1)) * (C + 1) + (e >> LOGN)] = mk<R>((R)0.5 * xa[k], (R)0.5 * xb[k]);
-    }
-    sync();
     cplx<R> v[8];
 #pragma unroll
-    for (int s = 0; s < 8; ++s) v[s] = at(t + s * T);
-    sync();
+    for (int s = 0; s < 8; ++s) v[s] = mk<R>((R)0.5 * xa[s], (R)0.5 * xb[s]);
     if (p + 2 < nfields) fetch(p + 2);
     fft_pencil<R, N, true>(v, t, twr, at, sync);
     cplx<R> *oa = out + (size_t)p * nz * npen + q, *ob = oa + (size_t)nz * npen;
     const bool two = p + 1 < nfields;
     split_half<R, T, N>(v, t, nz - 1, at, [&](int, int z, cplx<R> ha, cplx<R> hb) {
-      if (q >= npen) return;
       oa[(size_t)z * npen] = ha;
       if (two) ob[(size_t)z * npen] = hb;
     });

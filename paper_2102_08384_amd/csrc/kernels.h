@@ -166,7 +166,7 @@ void launch_fy(hipStream_t s, int prec, int N, int inv, const void *in, void *ou
                int nplanes, int nkx, int rs, const int *ycnt, const int64_t *yoff, int64_t npen,
                const void *tw, const int *rowmask, const int *zlist, const DevNorm *norm,
                ColTune tune = ColTune(), const Batch *batch = nullptr);
-// c2c along z.  Full sets (goff null): out[p][moff[q] + kz], all N kz of every pencil.
+// c2c along z.  Full sets (goff null): out[p][(g N + kz) C + c] for pencil q = g C + c.
 // Sphere-pruned sets: out[p][goff[g] + slot * C + c] for pencil q = g C + c, slot as in Prune
 // (C = 128 bytes / complex size, the pencils per workgroup).  Field stride mstride.
 // planemask (may be null): empty z-planes of the input are read as zeros.
@@ -175,7 +175,7 @@ void launch_fy(hipStream_t s, int prec, int N, int inv, const void *in, void *ou
 // with `half` besides, the input holds the planes z = 0 .. N/2 of a field that is even in D, and plane -z
 // is the complex conjugate of plane z
 void launch_fz(hipStream_t s, int prec, int N, const void *in, void *out, int nfields,
-               int64_t npen, const PencilInfo *pinfo, const int64_t *moff, const int64_t *goff,
+               int64_t npen, const PencilInfo *pinfo, const int64_t *goff,
                const int *gsize, int64_t mstride, const void *tw, const int *planemask,
                const int *fmap = nullptr, ColTune tune = ColTune(), const Batch *batch = nullptr,
                bool real_only = false, bool half = false);
@@ -219,7 +219,7 @@ bool mid_reweight_generated(int lmax, int order, int all_parity);
 int mid_reweight_nfields(int lmax, int order, int all_parity);
 
 // ---- inverse path (inverse.hip) ----
-// Bisector xi: inverse z pass of the real targets in[t][q * N + kz] (pencil-major), onto the planes
+// Bisector xi: inverse z pass of the real targets in[t][..] (laid out as launch_fz's full sets), onto the planes
 // z = 0 .. nz - 1 <= N/2: out[t][z][q].
 void launch_iz(hipStream_t s, int prec, int N, const void *in, void *out, int nfields, int64_t npen, int nz,
                const void *tw);
@@ -277,9 +277,9 @@ void launch_mix(hipStream_t s, int prec, int N, int lmax, int order, int all_par
 // about what the halves save (whole estimates: 15 g fields 290.2 -> 290.6 us, 73 419 -> 406 us, 130
 // 564 -> 541 us), at 128^3 they gain 7 to 20%; smaller meshes are launch-bound throughout.
 constexpr int kMidHalfMesh = 64;
-// Bisector xi targets: T[t][i] = sum S Re(conj(R_p1) R_p2) / W(k)^2 over the full
-// pencil-major spectra (i = q * N + kz, q = ky * rs + kx), written as real values (generated).
-// Field p of spec starts at p * mstride; target t of T at t * nmodes.
+// Bisector xi targets: T[t][i] = sum S Re(conj(R_p1) R_p2) / W(k)^2 over full spectra, i the mode index of
+// launch_fz's full sets, written as real values (generated).  Field p of spec starts at p * mstride;
+// target t of T at t * nmodes.
 void launch_targets(hipStream_t s, int prec, int N, int lmax, int bmax, const void *spec, int64_t nmodes,
                     int64_t mstride, int rs, const void *winv, void *T);
 // Midpoint P contraction: E_l = sum_nu y_l^nu(k^) (G_{l nu}(k) + A_{l nu}(k)) on the k-sphere modes; G

@@ -495,15 +495,16 @@ void launch_fy(hipStream_t s, int prec, int N, int inv, const void *in, void *ou
   }
 }
 
-// Output layouts (see Prune): full sets pencil-major, written through an LDS transpose so that
-// each pencil's run leaves as whole wavefront stores; sphere-pruned sets (goff != null) grouped
-// as [kz slot][pencil], so the C lanes of one kz write one 128-byte line straight from registers.
-// (REAL_ONLY: the real parts alone, for spectra whose imaginary parts no shell sum reads)
-template <typename R, int N, bool GROUPED, bool REAL_ONLY>
+// Output layout (see Prune): groups of C pencils, each [kz slot][pencil], so the C lanes of one kz write
+// one 128-byte line straight from registers.  Sphere-pruned sets keep the slots of the group's kz
+// extent; full sets (goff null) every kz.  (Full sets used to leave pencil by pencil through an LDS
+// transpose; a bisector xi_l at 512^3: 9.03 -> 8.63 ms, and the inverse z pass of the targets, in the same
+// layout, 1.14 -> 1.03 ms, at 128^3 66 -> 34 us.)
+// REAL_ONLY: the real parts alone, for spectra whose imaginary parts no shell sum reads.
+template <typename R, int N, bool REAL_ONLY>
 __global__ void __launch_bounds__((ColShape<R, N>::THREADS))
 k_fz(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, int nfields, int fpb, int64_t npen,
-     const PencilInfo *__restrict__ pinfo, const int64_t *__restrict__ moff, const int64_t *__restrict__ goff,
-     const int *__restrict__ gsize, int64_t mstride, const cplx<R> *__restrict__ tw,
+     const PencilInfo *__restrict__ pinfo, const int64_t *__restrict__ goff, const int *__restrict__ gsize, int64_t mstride, const cplx<R> *__restrict__ tw,
      const int *__restrict__ planemask, const int *__restrict__ fmap, int half, const Batch ba) {
   constexpr int T = ColShape<R, N>::T, C = ColShape<R, N>::C, NT = ColShape<R, N>::THREADS;
   if (ba.n) {  // catalog blockIdx.z of a batch
@@ -512,9 +513,8 @@ k_fz(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, int nfields, int
     out = (cplx<R> *)bs.A;
     planemask = bs.planemask;
   }
-  constexpr int LB = N * (C + 1);  // one exchange buffer; grouped: two alternate
-  __shared__ cplx<R> lds[GROUPED ? 2 * LB : LB];
-  __shared__ int st[C + 1];                      // full sets: first output mode of each pencil
+  constexpr int LB = N * (C + 1);  // one exchange buffer; two alternate
+  __shared__ cplx<R> lds[2 * LB];
   __shared__ int msk[N];
   const int c = threadIdx.x % C, t = threadIdx.x / C;
   const int64_t q0 = (int64_t)blockIdx.x * C;
@@ -525,25 +525,12 @@ k_fz(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, int nfields, int
   FftTw<R, N> twr;
   twr.load(t, tw);
   for (int i = threadIdx.x; i < N; i += NT) msk[i] = planemask ? planemask[i] : 1;
-  int64_t m0;
-  int S = 0;
-  if constexpr (GROUPED) {
-    m0 = goff[blockIdx.x];
-    S = gsize[blockIdx.x];
-  } else {
-    m0 = moff[q0];
-    if (threadIdx.x <= C) {
-      const int64_t qq = q0 + threadIdx.x;
-      const int64_t e = (qq < npen) ? moff[qq] : moff[npen - 1] + pinfo[npen - 1].kzcnt;
-      st[threadIdx.x] = (int)(e - m0);
-    }
-  }
+  const int64_t m0 = goff ? goff[blockIdx.x] : (int64_t)blockIdx.x * N * C;
+  const int S = goff ? gsize[blockIdx.x] : N;
   const bool has = q < npen && pinfo[q].kzcnt > 0;  // padding pencils hold no modes
   wait_vmem();
   __syncthreads();
-  if constexpr (GROUPED) {
-    if (S == 0) return;  // no pencil of the group holds a mode (uniform, after the last barrier)
-  }
+  if (S == 0) return;  // no pencil of the group holds a mode (uniform, after the last barrier)
   auto load = [&](int p, cplx<R> *v) {
     if constexpr (REAL_ONLY) {
       if (half) {  // (the imaginary parts of the planes 0 and N/2 only reach the dropped part)
@@ -568,7 +555,7 @@ k_fz(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, int nfields, int
   auto at = [c, &lb](int i) -> cplx<R> & { return lds[lb * LB + i * (C + 1) + c]; };
   auto sync = []() { __syncthreads(); };
   auto flip = [&lb]() { lb ^= 1; };
-  // grouped: slot of kz = t + s T, or -1 outside the group's kz extent
+  // slot of kz = t + s T, or -1 outside the group's kz extent
   const int h = (S - 1) / 2;
   int slot[8];
 #pragma unroll
@@ -576,9 +563,6 @@ k_fz(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, int nfields, int
     const int kz = t + s * T;
     slot[s] = (S == N || kz <= h) ? kz : (kz >= N - h ? kz - N + S : -1);
   }
-  // full: pencil oc goes out through its own T lanes (a whole wavefront when T = 64)
-  const int oc = threadIdx.x / T, oj = threadIdx.x % T;
-  const int obase = GROUPED ? 0 : st[oc], ocnt = GROUPED ? 0 : st[oc + 1] - obase;
   cplx<R> nxt[8];
   load(p0, nxt);
   for (int p = p0; p < p1; ++p) {
@@ -586,34 +570,23 @@ k_fz(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, int nfields, int
 #pragma unroll
     for (int s = 0; s < 8; ++s) v[s] = nxt[s];
     if (p + 1 < p1) load(p + 1, nxt);
-    if constexpr (GROUPED) fft_pencil_db<R, N, false>(v, t, twr, at, sync, flip);
-    else fft_pencil<R, N, false>(v, t, twr, at, sync);
-    if constexpr (GROUPED) {
-      // fmap: output field of input field p (a group of fields transformed at a time)
-      const size_t o = (size_t)(fmap ? fmap[p] : p) * mstride + m0 + c;
-      cplx<R> *dst = out + o;
-      R *rdst = reinterpret_cast<R *>(out) + o;
+    fft_pencil_db<R, N, false>(v, t, twr, at, sync, flip);
+    // fmap: output field of input field p (a group of fields transformed at a time)
+    const size_t o = (size_t)(fmap ? fmap[p] : p) * mstride + m0 + c;
+    cplx<R> *dst = out + o;
+    R *rdst = reinterpret_cast<R *>(out) + o;
 #pragma unroll
-      for (int s = 0; s < 8; ++s)
-        if (slot[s] >= 0) {
-          if constexpr (REAL_ONLY) rdst[(size_t)slot[s] * C] = v[s].x;
-          else store_nt<!keep_lines(N)>(dst + (size_t)slot[s] * C, v[s]);
-        }
-    } else {
-#pragma unroll
-      for (int s = 0; s < 8; ++s) at(t + s * T) = v[s];
-      __syncthreads();
-      // the block's pencils own one contiguous run of modes starting at m0, all N kz each
-      cplx<R> *dst = out + (size_t)p * mstride + m0 + obase;
-      for (int j = oj; j < ocnt; j += T) store_nt<!keep_lines(N)>(dst + j, lds[j * (C + 1) + oc]);
-      __syncthreads();  // LDS reads done before the next transform writes
-    }
+    for (int s = 0; s < 8; ++s)
+      if (slot[s] >= 0) {
+        if constexpr (REAL_ONLY) rdst[(size_t)slot[s] * C] = v[s].x;
+        else store_nt<!keep_lines(N)>(dst + (size_t)slot[s] * C, v[s]);
+      }
   }
 }
 
 template <typename R, int N>
 static void fz_launch(hipStream_t s, const void *in, void *out, int nfields, int64_t npen,
-                      const PencilInfo *pinfo, const int64_t *moff, const int64_t *goff, const int *gsize,
+                      const PencilInfo *pinfo, const int64_t *goff, const int *gsize,
                       int64_t mstride, const void *tw, const int *planemask, const int *fmap,
                       ColTune tune, const Batch *batch, bool real_only, bool half) {
   constexpr int C = ColShape<R, N>::C;
@@ -630,30 +603,26 @@ static void fz_launch(hipStream_t s, const void *in, void *out, int nfields, int
   }
   fpb = std::min(fpb, nfields);
   dim3 grid(ng, (nfields + fpb - 1) / fpb, nb);
-  if (goff && real_only)
-    hipLaunchKernelGGL((k_fz<R, N, true, true>), grid, dim3(ColShape<R, N>::THREADS), 0, s, (const cplx<R> *)in,
-                       (cplx<R> *)out, nfields, fpb, npen, pinfo, moff, goff, gsize, mstride, (const cplx<R> *)tw,
-                       planemask, fmap, half, ba);
-  else if (goff)
-    hipLaunchKernelGGL((k_fz<R, N, true, false>), grid, dim3(ColShape<R, N>::THREADS), 0, s, (const cplx<R> *)in,
-                       (cplx<R> *)out, nfields, fpb, npen, pinfo, moff, goff, gsize, mstride, (const cplx<R> *)tw,
-                       planemask, fmap, half, ba);
+  if (real_only)
+    hipLaunchKernelGGL((k_fz<R, N, true>), grid, dim3(ColShape<R, N>::THREADS), 0, s, (const cplx<R> *)in,
+                       (cplx<R> *)out, nfields, fpb, npen, pinfo, goff, gsize, mstride, (const cplx<R> *)tw, planemask,
+                       fmap, half, ba);
   else
-    hipLaunchKernelGGL((k_fz<R, N, false, false>), grid, dim3(ColShape<R, N>::THREADS), 0, s, (const cplx<R> *)in,
-                       (cplx<R> *)out, nfields, fpb, npen, pinfo, moff, goff, gsize, mstride, (const cplx<R> *)tw,
-                       planemask, (const int *)nullptr, 0, ba);
+    hipLaunchKernelGGL((k_fz<R, N, false>), grid, dim3(ColShape<R, N>::THREADS), 0, s, (const cplx<R> *)in,
+                       (cplx<R> *)out, nfields, fpb, npen, pinfo, goff, gsize, mstride, (const cplx<R> *)tw, planemask,
+                       fmap, half, ba);
 }
 
 void launch_fz(hipStream_t s, int prec, int N, const void *in, void *out, int nfields, int64_t npen,
-               const PencilInfo *pinfo, const int64_t *moff, const int64_t *goff, const int *gsize,
+               const PencilInfo *pinfo, const int64_t *goff, const int *gsize,
                int64_t mstride, const void *tw, const int *planemask, const int *fmap, ColTune tune,
                const Batch *batch, bool real_only, bool half) {
   if (nfields <= 0 || npen <= 0) return;
   if (prec == 0) {
-    PW_DISPATCH_N(fz_launch, float, s, in, out, nfields, npen, pinfo, moff, goff, gsize, mstride, tw, planemask,
+    PW_DISPATCH_N(fz_launch, float, s, in, out, nfields, npen, pinfo, goff, gsize, mstride, tw, planemask,
                   fmap, tune, batch, real_only, half)
   } else {
-    PW_DISPATCH_N(fz_launch, double, s, in, out, nfields, npen, pinfo, moff, goff, gsize, mstride, tw, planemask,
+    PW_DISPATCH_N(fz_launch, double, s, in, out, nfields, npen, pinfo, goff, gsize, mstride, tw, planemask,
                   fmap, tune, batch, real_only, half)
   }
 }

@@ -57,9 +57,8 @@ Prune make_prune(int N, int64_t K2, bool full, bool coords, int prec) {
     p.npen_real += cnt;
   }
   p.npen = off;
-  int64_t moff = 0;
+  int64_t nmodes = 0;
   p.pinfo.reserve((size_t)p.npen);
-  p.moff.reserve((size_t)p.npen);
   for (int ky = 0; ky < N; ++ky) {
     int64_t sy = signed_idx(ky, N);
     const int slots = full ? p.rs : (int)padq(p.ycnt[ky]);
@@ -75,18 +74,13 @@ Prune make_prune(int N, int64_t K2, bool full, bool coords, int prec) {
         cnt = (2 * kzm + 1 >= N) ? N : (int)(2 * kzm + 1);
       }
       p.pinfo.push_back(PencilInfo{kx, ky, cnt, 0});
-      p.moff.push_back(moff);
-      if (coords && full && cnt > 0) {
-        for (int kz = 0; kz < N; ++kz)
-          p.modecoord.push_back((uint32_t)kx | ((uint32_t)ky << 11) | ((uint32_t)kz << 22));
-      }
-      moff += cnt;
+      nmodes += cnt;
       p.nretained += cnt;
     }
   }
   if (full) {
-    p.nmodes = moff;
-    p.mstride = padq(moff);
+    p.nmodes = nmodes;
+    p.mstride = padq(nmodes);
     return p;
   }
   // Sphere-pruned: groups of Q adjacent pencils (the z pass transforms Q pencils per workgroup;
@@ -536,7 +530,7 @@ size_t table_bytes(const HostPlan &h) {
   const int ts = tile_size(h.N), nt = h.N / ts;
   size_t b = (h.fwd.modecoord.size() + h.sph.modecoord.size() + h.bin_of_s2.size()) * 4 +
              (h.fwd.pinfo.size() + h.sph.pinfo.size()) * sizeof(PencilInfo) +
-             (h.fwd.moff.size() + h.sph.moff.size() + h.fwd.goff.size() + h.sph.goff.size() + h.fwd.yoff.size() +
+             (h.fwd.goff.size() + h.sph.goff.size() + h.fwd.yoff.size() +
               h.sph.yoff.size() + h.iyoff.size()) * 8 +
              (h.fwd.ycnt.size() + h.sph.ycnt.size() + h.fwd.gsize.size() + h.sph.gsize.size() + h.zrank.size() +
               h.zidx.size() + h.yidx.size() + h.iycnt.size() + h.odd_of.size()) * 4;

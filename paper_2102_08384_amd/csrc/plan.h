@@ -48,9 +48,8 @@ struct Prune {
   int64_t npen = 0;                 // pencils per y-pass plane, padding included
   int64_t npen_real = 0;            // retained pencils (sum of ycnt)
   std::vector<PencilInfo> pinfo;    // [npen]
-  std::vector<int64_t> moff;        // [npen] (full sets: pencil q holds modes [moff[q], +N))
-  // z-pass output.  Full sets: pencil-major, kz fastest.  Sphere-pruned sets: groups of `grp`
-  // adjacent pencils, each stored as [kz slot][pencil of the group]: slot j of group g holds
+  // z-pass output: groups of `grp` adjacent pencils.  Full sets: each [kz][pencil of the group], every
+  // kz.  Sphere-pruned sets: each stored as [kz slot][pencil of the group]: slot j of group g holds
   // kz = j for j <= h_g and kz = N - (gsize[g] - j) above (all N kz when gsize[g] == N), with
   // h_g = (gsize[g] - 1) / 2 the largest half-count of the group's pencils.  Slots outside a
   // pencil's own sphere (and padding pencils) carry the coordinate kModeNone.
@@ -159,7 +158,6 @@ struct DevPrune {
   int *ycnt = nullptr;
   int64_t *yoff = nullptr;
   PencilInfo *pinfo = nullptr;
-  int64_t *moff = nullptr;
   uint32_t *modecoord = nullptr;
   int64_t *goff = nullptr;   // sphere-pruned sets only
   int *gsize = nullptr;
