@@ -105,17 +105,19 @@ struct ShPair8 {
 
 // One block = ROWS rows (z, y) of N cells; lane t of a row holds cells x = t + s*T.  For every
 // job, two real fields (F (u/2r)^alpha y_J^mu) go through one complex FFT Z = FFT(a + i b) and are
-// separated as A(k) = (Z(k) + conj Z(N-k)) / 2, B(k) = (Z(k) - conj Z(N-k)) / 2i for kx < nkx.  When a row is one wavefront (T = 64) the FFT's
-// exchanges need only wavefront ordering and Z(N-k) comes from the partner lane by a cross-lane
-// permute; otherwise the rows of the block share barriers and the separation reads LDS.
-// FP32 at N = 512 fits three wavefronts per SIMD without spills (FP64 would spill).
+// separated as A(k) = (Z(k) + conj Z(N-k)) / 2, B(k) = (Z(k) - conj Z(N-k)) / 2i for kx < nkx.  A row
+// never spans wavefronts (T <= 64), so the FFT's exchanges need only wavefront ordering and Z(N-k)
+// comes from the partner lane by a cross-lane permute.  (Below 512 the rows of a workgroup used to
+// share barriers and separate through LDS: 256^3 FP64 0.88 -> 0.71 ms, FP32 midpoint 0.25 -> 0.21 ms,
+// 128^3 65 -> 54 us.)
+// FP32 at N = 256 and 512 fits three wavefronts per SIMD (at most two registers spilled; FP64 would spill).
 // RADIAL: jobs may carry radial weights (u/2r)^alpha (midpoint fields), so each value keeps
 // 1/r; otherwise (bisector fields) it keeps z/r, the only radial quantity the harmonics need,
 // and 1/r is recomputed when the recurrence changes m.  Both fields of a job enter the
 // transform scaled by 1/2 (exactly), which is the factor of the two-real-field separation.
 template <typename R, int N, bool RADIAL, int ROWS = FxShape<N>::ROWS>
 __global__ void __launch_bounds__(ROWS * FxShape<N>::T)
-__attribute__((amdgpu_waves_per_eu((sizeof(R) == 4 && N == 512) ? 3 : 1, 8)))
+__attribute__((amdgpu_waves_per_eu((sizeof(R) == 4 && N >= 256) ? 3 : 1, 8)))
 k_fx(const R *__restrict__ mesh, cplx<R> *__restrict__ out, const FieldJob *__restrict__ jobs,
      int njobs, int nkx, int rs, R b0x, R b0y, R b0z, R H, R uhalf, const cplx<R> *__restrict__ tw,
      const int *__restrict__ rowlist, const DevNorm *__restrict__ norm, const Batch ba) {
@@ -127,7 +129,7 @@ k_fx(const R *__restrict__ mesh, cplx<R> *__restrict__ out, const FieldJob *__re
     rowlist = bs.rowlist;
     norm = bs.norm;
   }
-  constexpr bool WAVE = (T == 64), NT = !keep_lines(N);
+  constexpr bool NT = !keep_lines(N);
   constexpr int LN = N + N / 8;
   __shared__ cplx<R> lds[ROWS * LN];
   const int rl = threadIdx.x / T, t = threadIdx.x % T;
@@ -140,14 +142,13 @@ k_fx(const R *__restrict__ mesh, cplx<R> *__restrict__ out, const FieldJob *__re
     live = row < nr;
     row = live ? rowlist[row] : 0;
   }
-  if constexpr (WAVE) {
-    if (!live) return;  // a whole wavefront, and no block-wide barrier follows
-  }
+  if (!live) return;  // (whole groups of T lanes, and no block-wide barrier follows)
   const int y = row & (N - 1), z = row / N;
+  const int partner = (threadIdx.x & 63 & ~(T - 1)) | ((T - t) & (T - 1));  // lane T - t of the row
   cplx<R> *my = lds + rl * LN;
   auto at = [my](int i) -> cplx<R> & { return my[i + (i >> 3)]; };
   auto sync = []() {
-    if constexpr (WAVE) wave_lds_sync(); else __syncthreads();
+    wave_lds_sync();
   };
 
   // per value: density and 1/r (RADIAL) or z/r (the direction is rebuilt from the position
@@ -260,47 +261,27 @@ k_fx(const R *__restrict__ mesh, cplx<R> *__restrict__ out, const FieldJob *__re
     cplx<R> *oa = out + (size_t)J.pa * fstride + (size_t)row * rs;
     cplx<R> *ob = out + (size_t)(J.pb < 0 ? 0 : J.pb) * fstride + (size_t)row * rs;
     const bool hb = J.pb >= 0;
-    if constexpr (WAVE) {
-      // lane t holds Z(t + 64 s).  Z(N - k) for k = t + 64 s, s < 4: lane (64 - t) & 63, its
-      // v[7 - s] (t > 0) or v[(8 - s) & 7] (lane 0); every lane publishes the value its
-      // partner needs.  k = 256 (s = 4) is lane 0's own v[4]; 256 < k < rs is padding.
-      // (the inputs carry the separation's factor 1/2)
-      const int partner = (64 - t) & 63;
+    // lane t holds Z(t + s T).  Z(N - k) for k = t + s T, s < 4: lane T - t, its v[7 - s], or (t = 0) lane
+    // 0's own v[(8 - s) & 7]; every lane publishes the value its partner needs.  k = N/2 (s = 4) is
+    // lane 0's own v[4]; N/2 < k < rs is padding.  (the inputs carry the separation's factor 1/2)
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        if (64 * s >= rs) break;  // uniform: no lane stores at or beyond the padded row
-        const cplx<R> pub = (t == 0) ? v[(8 - s) & 7] : v[7 - s];
-        const cplx<R> b = lane_fetch<R>(partner, pub);
-        const cplx<R> a = v[s];
-        const int kx = t + 64 * s;
-        if (kx < rs) {
-          const bool keep = kx < nkx;
-          store_nt<NT>(oa + kx, keep ? mk<R>(a.x + b.x, a.y - b.y) : mk<R>(0, 0));
-          if (hb) store_nt<NT>(ob + kx, keep ? mk<R>(a.y + b.y, b.x - a.x) : mk<R>(0, 0));
-        }
+    for (int s = 0; s < 4; ++s) {
+      if (T * s >= rs) break;  // uniform: no lane stores at or beyond the padded row
+      const cplx<R> pub = (t == 0) ? v[(8 - s) & 7] : v[7 - s];
+      const cplx<R> b = lane_fetch<R>(partner, pub);
+      const cplx<R> a = v[s];
+      const int kx = t + T * s;
+      if (kx < rs) {
+        const bool keep = kx < nkx;
+        store_nt<NT>(oa + kx, keep ? mk<R>(a.x + b.x, a.y - b.y) : mk<R>(0, 0));
+        if (hb) store_nt<NT>(ob + kx, keep ? mk<R>(a.y + b.y, b.x - a.x) : mk<R>(0, 0));
       }
-      const int kx = 256 + t;
-      if (256 < rs && kx < rs) {
-        const bool keep = (t == 0) && kx < nkx;  // Z(256) pairs with itself
-        const cplx<R> a = v[4];
-        oa[kx] = keep ? mk<R>(a.x + a.x, (R)0) : mk<R>(0, 0);
-        if (hb) ob[kx] = keep ? mk<R>(a.y + a.y, (R)0) : mk<R>(0, 0);
-      }
-    } else {
-#pragma unroll
-      for (int s = 0; s < 8; ++s) at(t + s * T) = v[s];
-      __syncthreads();
-      for (int kx = t; live && kx < rs; kx += T) {
-        if (kx >= nkx) {  // padding to the 128-byte row stride: whole-line writes
-          oa[kx] = mk<R>(0, 0);
-          if (hb) ob[kx] = mk<R>(0, 0);
-          continue;
-        }
-        const cplx<R> a = at(kx), b = at((N - kx) & (N - 1));
-        store_nt<NT>(oa + kx, mk<R>(a.x + b.x, a.y - b.y));
-        if (hb) store_nt<NT>(ob + kx, mk<R>(a.y + b.y, b.x - a.x));
-      }
-      __syncthreads();
+    }
+    for (int kx = N / 2 + t; kx < rs; kx += T) {
+      const bool keep = kx == N / 2 && kx < nkx;  // Z(N/2) pairs with itself
+      const cplx<R> a = v[4];
+      oa[kx] = keep ? mk<R>(a.x + a.x, (R)0) : mk<R>(0, 0);
+      if (hb) ob[kx] = keep ? mk<R>(a.y + a.y, (R)0) : mk<R>(0, 0);
     }
   }
 }
