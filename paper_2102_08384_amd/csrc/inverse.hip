@@ -615,7 +615,9 @@ k_ix(const cplx<R> *__restrict__ in, int rs, const FieldJob *__restrict__ jobs, 
   ShRec8<R> rec;
   rec.init();
   const size_t fstride = (size_t)nrows * rs;  // rows padded to rs
-  for (int jb = 0; jb < njobs; ++jb) {
+  // this workgroup's share of the jobs (grid y): the sums are linear in them
+  const int jb0 = njobs * (int)blockIdx.y / (int)gridDim.y, jb1 = njobs * ((int)blockIdx.y + 1) / (int)gridDim.y;
+  for (int jb = jb0; jb < jb1; ++jb) {
     const FieldJob J = jobs[jb];
     const cplx<R> *ha = in + (size_t)J.pa * fstride + (size_t)row * rs;
     const cplx<R> *hb = in + (size_t)(J.pb < 0 ? 0 : J.pb) * fstride + (size_t)row * rs;
@@ -693,8 +695,10 @@ k_ix(const cplx<R> *__restrict__ in, int rs, const FieldJob *__restrict__ jobs, 
 #pragma unroll
     for (int l = 0; l < kMaxEll; ++l)
       if (l < nell) atomicAdd(&bacc[l * nbins + b], mult * (double)(X[l][s] * scale));
-    atomicAdd(&bacc[nell * nbins + b], mult);
-    atomicAdd(&bacc[(nell + 1) * nbins + b], mult * Hd * sqrt(s2));
+    if (blockIdx.y == 0) {  // each cell is counted once
+      atomicAdd(&bacc[nell * nbins + b], mult);
+      atomicAdd(&bacc[(nell + 1) * nbins + b], mult * Hd * sqrt(s2));
+    }
   }
   sync();
   for (int i = threadIdx.x; i < nacc; i += blockDim.x)
@@ -707,7 +711,12 @@ static void ix_launch(hipStream_t s, const void *in, int rs, const FieldJob *job
                       const int *bin_of_s2, int64_t n_s2, int nbins, double *acc, const void *tw) {
   constexpr int ROWS = FxShape<N>::ROWS;
   const int64_t nrows = (int64_t)nz * ny;
-  dim3 grid((unsigned)((nrows + ROWS - 1) / ROWS));
+  // Few rows lie inside the r-bins of a coarse mesh (about 200 at 128^3 for bins to 200 in a box of 2900:
+  // 24 workgroups), each a chain over every job: the jobs are shared out over grid y until a thousand
+  // workgroups run, at least three jobs each: with 28 targets 80 -> 30 us.  At 512^3 the rows alone fill the chip (640 workgroups of two waves per SIMD) and
+  // sharing them out three ways was slower (1.22 -> 1.27 ms).
+  const unsigned nblk = (unsigned)((nrows + ROWS - 1) / ROWS);
+  dim3 grid(nblk, std::max(1u, std::min(1024u / nblk, (unsigned)njobs / 3u)));
   const size_t sh = (size_t)(nell + 2) * nbins * sizeof(double);
   hipLaunchKernelGGL((k_ix<R, N>), grid, dim3(FxShape<N>::THREADS), sh, s, (const cplx<R> *)in, rs, jobs, njobs,
                      (const R *)coef, nell, half, nz, ny, zidx, yidx, (R)(H / unit), H, (R)scale, bin_of_s2, n_s2, nbins, acc,
