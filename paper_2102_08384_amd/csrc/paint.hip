@@ -18,6 +18,8 @@
 // No global atomics touch the mesh: each node is written once with a plain store.
 #include "kernels.h"
 
+#include <algorithm>
+
 namespace pw {
 
 
@@ -455,22 +457,28 @@ k_sort_scatter(const RG *__restrict__ gx, const RR *__restrict__ rx, int64_t ng,
 // split does not show in the mesh).  A part holds at least 2048 records (zeroing and storing a block
 // cost about as much as depositing 1000) and a 512th of the catalog (two workgroups per CU in all:
 // with a 2048-record limit alone, 10^3 occupied tiles of 6 10^3 records were cut in three and the
-// stage went from 0.40 to 0.50 ms).  Eight catalogs of 6 10^5 particles on 64^3: 2.09 -> 1.4 ms for the
-// whole batch; 6 10^6 on a doubled 256^3 box: paint stage 0.56 -> 0.43 ms.
-__device__ __forceinline__ int tile_parts(int len, int total, int most) {
-  const int per = max(2048, total / 512);
-  return min((len + per - 1) / per, most);
+// stage went from 0.40 to 0.50 ms).  `parts` has room for `room` blocks, shared evenly by the occupied
+// tiles.  Eight catalogs of 6 10^5 particles on 64^3: 2.09 -> 1.4 ms for the whole batch; 6 10^6 on a
+// doubled 256^3 box: paint stage 0.56 -> 0.43 ms.
+struct PartShare {
+  int per, most;  // records of a part; parts of a tile at most
+};
+__device__ __forceinline__ PartShare part_share(const int *offsets, const int *slot, int ntiles, int most, int room) {
+  const int occ = slot[ntiles];
+  return PartShare{max(2048, offsets[ntiles] / 512), max(1, min(most, room / max(occ, 1)))};
 }
+__device__ __forceinline__ int tile_parts(int len, PartShare sh) { return min((len + sh.per - 1) / sh.per, sh.most); }
 
 template <typename RM, int ASSIGN>
 __global__ void __launch_bounds__(512) k_tile_paint(int ts, const int *__restrict__ offsets,
                                                     const int *__restrict__ slot,
                                                     const typename Rec4<RM>::T *__restrict__ rec,
                                                     const DevNorm *__restrict__ norm, RM *__restrict__ blocks,
-                                                    long long *__restrict__ parts) {
+                                                    long long *__restrict__ parts, int room) {
   const int tile = blockIdx.x;
+  const PartShare sh = part_share(offsets, slot, gridDim.x, gridDim.y, room);
   const int beg0 = offsets[tile], len = offsets[tile + 1] - beg0;
-  const int np = tile_parts(len, offsets[gridDim.x], gridDim.y), part = blockIdx.y;
+  const int np = tile_parts(len, sh), part = blockIdx.y;
   if (part >= np) return;  // uniform for the block (len 0: no parts)
   const int beg = beg0 + (int)((int64_t)len * part / np), end = beg0 + (int)((int64_t)len * (part + 1) / np);
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -529,7 +537,7 @@ __global__ void __launch_bounds__(512) k_tile_paint(int ts, const int *__restric
   }
   __syncthreads();
   if (np > 1) {
-    long long *dst = parts + ((size_t)slot[tile] * gridDim.y + part) * E3;
+    long long *dst = parts + ((size_t)slot[tile] * sh.most + part) * E3;
     for (int c = threadIdx.x; c < E3; c += blockDim.x) dst[c] = (long long)acc[c];
     return;
   }
@@ -543,13 +551,15 @@ __global__ void __launch_bounds__(512) k_tile_paint(int ts, const int *__restric
 template <typename RM>
 __global__ void __launch_bounds__(256) k_tile_combine(int ts, int most, const int *__restrict__ offsets,
                                                       const int *__restrict__ slot, const DevNorm *__restrict__ norm,
-                                                      const long long *__restrict__ parts, RM *__restrict__ blocks) {
+                                                      const long long *__restrict__ parts, int room,
+                                                      RM *__restrict__ blocks) {
   const int tile = blockIdx.x;
-  const int np = tile_parts(offsets[tile + 1] - offsets[tile], offsets[gridDim.x], most);
+  const PartShare sh = part_share(offsets, slot, gridDim.x, most, room);
+  const int np = tile_parts(offsets[tile + 1] - offsets[tile], sh);
   if (np < 2) return;  // uniform
   const int E = ts + 2, E3 = E * E * E;
   const double inv = 1.0 / (sizeof(RM) == 4 ? norm->fix_scale * (1.0 / 2048.0) : norm->fix_scale);
-  const long long *src = parts + (size_t)slot[tile] * most * E3;
+  const long long *src = parts + (size_t)slot[tile] * sh.most * E3;
   RM *dst = blocks + (size_t)slot[tile] * E3;
   for (int c = blockIdx.y * blockDim.x + threadIdx.x; c < E3; c += gridDim.y * blockDim.x) {
     long long v = 0;
@@ -843,17 +853,13 @@ static int ilog2(int v) {
   return r;
 }
 
-// Parts of a tile: none on meshes whose tiles outnumber the CUs many times, or for catalogs too small
-// to fill a part per tile and CU; else up to 16 while their blocks fit the scratch.  (4096 tiles is
-// 256^3: a survey there occupies a few hundred tiles of tens of thousands of particles.)
-static int paint_parts(int N, int64_t n_part, size_t scratch_bytes) {
-  const int ts = tile_size(N);
-  const int64_t ntiles = (int64_t)(N / ts) * (N / ts) * (N / ts);
-  if (ntiles > 4096 || n_part < (int64_t)kSortNominalCUs * 1024) return 1;
-  const size_t block = (size_t)(ts + 2) * (ts + 2) * (ts + 2) * sizeof(long long);
-  const int64_t fit = (int64_t)(scratch_bytes / block) / ntiles;
-  const int64_t most = ntiles > 512 ? 8 : 16;  // (workgroups without a part still have to be started)
-  return (int)(fit < 1 ? 1 : (fit > most ? most : fit));
+// Parts of a tile at most: 1 (no second launch) on meshes whose tiles outnumber the CUs many times, for
+// catalogs too thin to fill parts (128^3, 3.6 10^5 particles, whole estimates: 170 us whole tiles, 178
+// in parts; 1.65 10^6: 290 and 279).
+static int paint_parts(int64_t ntiles, int64_t n_part, int64_t room) {
+  if (ntiles > 4096 || n_part < kSortNominalCUs * 1024 || n_part < ntiles * (ntiles > 512 ? 256 : 1024)) return 1;
+  if (room < 2) return 1;
+  return ntiles > 512 ? 8 : 16;  // (workgroups without a part still have to be started)
 }
 
 void launch_tile_paint(hipStream_t s, int prec, int N, int assign, int64_t n_part, const int *offsets, const int *slot,
@@ -864,17 +870,18 @@ void launch_tile_paint(hipStream_t s, int prec, int N, int assign, int64_t n_par
   const unsigned ntiles = (unsigned)(nt * nt * nt);
   const size_t E3 = (size_t)(ts + 2) * (ts + 2) * (ts + 2);
   const int threads = (tune.threads == 128 || tune.threads == 512) ? tune.threads : 256;
-  const int most = paint_parts(N, n_part, scratch_bytes);
+  const int room = (int)std::min<size_t>(scratch_bytes / (E3 * sizeof(long long)), 1u << 30);
+  const int most = paint_parts(ntiles, n_part, room);
 #define PW_TP(RM, A)                                                                              \
   hipLaunchKernelGGL((k_tile_paint<RM, A>), dim3(ntiles, most), dim3(threads), E3 * sizeof(unsigned long long), s, \
-                     ts, offsets, slot, (const typename Rec4<RM>::T *)records, norm, (RM *)blocks, (long long *)scratch)
+                     ts, offsets, slot, (const typename Rec4<RM>::T *)records, norm, (RM *)blocks, (long long *)scratch, room)
   if (prec == 0) { if (assign == 2) PW_TP(float, 2); else PW_TP(float, 3); }
   else { if (assign == 2) PW_TP(double, 2); else PW_TP(double, 3); }
 #undef PW_TP
   if (most < 2) return;
 #define PW_TC(RM)                                                                                             \
   hipLaunchKernelGGL(k_tile_combine<RM>, dim3(ntiles, ntiles > 512 ? 3 : 12), dim3(256), 0, s, ts, most, offsets, slot, norm,       \
-                     (const long long *)scratch, (RM *)blocks)
+                     (const long long *)scratch, room, (RM *)blocks)
   if (prec == 0) PW_TC(float);
   else PW_TC(double);
 #undef PW_TC
