@@ -235,7 +235,9 @@ void PW_CAT(launch_mix_, PW_MIX_N)(hipStream_t s, int prec, int lmax, int order,
     else mix_launch<double, PW_MIX_N, L, K, AP>(s, in, out, rs, nkx, rso, scale, Hu, tw, ax, ay);           \
     return;                                                                                      \
   }
+#ifndef PW_NO_SHAPES  // (a build for host checks launches nothing)
   PW_MIX_SHAPES(PW_MX)
+#endif
 #undef PW_MX
 }
 

@@ -114,7 +114,9 @@ void launch_nyq(hipStream_t s, int prec, int N, int lmax, int order, int all_par
                          (double *)ax, (double *)ay, N, scale, Hu);                                              \
     return;                                                                                                      \
   }
+#ifndef PW_NO_SHAPES  // (a build for host checks launches nothing)
   PW_MIX_SHAPES(PW_NQ)
+#endif
 #undef PW_NQ
 }
 
