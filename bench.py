@@ -41,11 +41,12 @@ METRIC = "bisector P_ℓ 512³ catalogs/s, served vs plain; p50/p99 latency; HBM
 HBM_PEAK_GBS = 8000.0
 COPY_BYTES = 1 << 30   # calibration copy: 1 GiB read + 1 GiB written
 KERNEL_NAMES = {"fx": "k_fx", "fy": "k_fy", "fz": "k_fz", "contract": "k_contract_bis_reg"}
-# midpoint P_l: forward passes, product + inverse z pass, inverse y/x passes, re-weighting, the
-# forward passes of the A fields and the k-space contraction
-KERNEL_NAMES_MID = {"fx": "k_fx", "fy": "k_fy", "fziz": "k_fziz", "iy": "k_fy", "ix_bin": "k_ix",
-                    "mix": "k_mix", "afy": "k_fy", "afz": "k_fz",
-                    "contract": "k_contract_mid"}
+# midpoint P_l: forward passes, product + inverse z pass, inverse y pass, the row pass (inverse x,
+# re-weighting, forward x of the A fields), A's y and z passes and the k-space contraction
+KERNEL_NAMES_MID = {"fx": "k_fx", "fy": "k_fy", "fziz": "k_fziz", "iy": "k_iy_half", "mix": "k_mix", "afy": "k_fy",
+                    "afz": "k_fz", "contract": "k_contract_mid"}
+# midpoint xi_l: forward passes, product + inverse z pass, inverse y pass, c2r x pass with r-binning
+KERNEL_NAMES_MXI = {"fx": "k_fx", "fy": "k_fy", "fziz": "k_fziz_half", "iy": "k_fy", "ix_bin": "k_ix"}
 # bisector xi_l: forward passes, per-mode targets, inverse z / y passes, c2r x pass with r-binning
 KERNEL_NAMES_BXI = {"fx": "k_fx", "fy": "k_fy", "fz": "k_fz", "targets": "k_targets", "iz": "k_iz",
                     "iy": "k_fy", "ix_bin": "k_ix"}
@@ -637,7 +638,9 @@ def main():
     rn = torch.from_numpy(ran["nbar"].astype(np.float32)).to(dev)
     cfg = workload_config(pw, a.workload, 1 if a.midpoint_parity == "all" else 0)
     cfg.memory_lean = 1 if a.memory_lean else 0
-    knames = (KERNEL_NAMES if wl.stat == "pk" else KERNEL_NAMES_BXI) if wl.los == "bisector" else KERNEL_NAMES_MID
+    pk = wl.stat == "pk"
+    knames = ((KERNEL_NAMES if pk else KERNEL_NAMES_BXI) if wl.los == "bisector"
+              else KERNEL_NAMES_MID if pk else KERNEL_NAMES_MXI)
     stream = torch.cuda.current_stream(dev)
     if a.copy_calibration:
         src = torch.empty(COPY_BYTES // 4, dtype=torch.float32, device=dev).fill_(1.0)
