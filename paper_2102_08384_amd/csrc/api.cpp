@@ -982,7 +982,7 @@ DevPlan *launch_estimate(pw_ctx *ctx, Lane &ln, const pw_config *cfg, const pw_c
     }
   } else {
     // Full sets: pencil q = ky * rs + kx, N values each (bisector xi: the z-pass spectra in A,
-    // pencil-major [p][q * N + kz]; midpoint: the y-pass output in B, [p][z][q]).
+    // in groups of pencils; midpoint: the y-pass output in B, [p][z][q]).
     const double inv_n3 = 1.0 / ncell;
     const int npl = h.nz;  // retained z planes of the inverse outputs
     const double zpart = (double)h.n_inv * npl * F.npen_real * csz;
