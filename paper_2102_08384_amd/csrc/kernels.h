@@ -64,11 +64,6 @@ void upload_sh_const(const ShConst &c);
 void upload_sh_const_inverse(const ShConst &c);
 void upload_sh_const_generated(const ShConst &c);
 
-// alpha_r, I, S, the range / extent flags and the painting scale from the partial rows of the
-// two catalogs (nblk_g, nblk_r rows of kScalarCols written by launch_sort_count).
-void launch_finalize_norm(hipStream_t s, const double *pg, int nblk_g, const double *pr, int nblk_r,
-                          DevNorm *norm, const double *b0, double L, int check_extent, int use_given,
-                          double ga, double gI, double gS);
 // Zero n_elems values: prec 0 float, 1 double, 2 int.
 void launch_fill(hipStream_t s, void *p, size_t n_elems, int prec);
 // Zero three int arrays in one launch.
@@ -110,7 +105,12 @@ SortLayout sort_layout(int N, int64_t n_gal, int64_t n_ran);
 void launch_sort_count(hipStream_t s, const SortLayout &L, const void *gx, int gdtype, const void *rx, int rdtype,
                        const void *rnbar, int64_t ng, int64_t nr, int N, const double *b0, double H, int assign,
                        int *chunk_hist, int *counts, double *part_g, double *part_r);
-void launch_tile_scan(hipStream_t s, const int *counts, int ntiles, int *offsets, int *slot);
+// After pass 1, in one launch: offsets and slot (exclusive scan of the tile counts, compact slots of the
+// occupied tiles), and alpha_r, I, S, the range / extent flags and the painting scale from the
+// partial rows of the two catalogs (nblk_g, nblk_r rows of kScalarCols).
+void launch_norm_scan(hipStream_t s, const int *counts, int ntiles, int *offsets, int *slot, const double *pg,
+                      int nblk_g, const double *pr, int nblk_r, DevNorm *norm, const double *b0, double L,
+                      int check_extent, int use_given, double ga, double gI, double gS);
 // Pass 2: tile-sorted records in the mesh precision (prec), randoms weighted by -alpha_r.
 // chunk_hist's counts become run bases in place (offsets: the tile offsets of the scan).
 void launch_sort_scatter(hipStream_t s, const SortLayout &L, const void *gx, int gdtype, const void *rx,
