@@ -826,15 +826,16 @@ void enqueue_paint(pw_ctx *ctx, Lane *ln, hipStream_t s, const DevPlan *dp, cons
   launch_sort_count(s, SL, gx, gal->dtype, rx, ran->dtype, rnb, gal->n, ran->n, h.N, cfg->box_origin, h.H,
                     cfg->assign, chunk_hist, dp->tile_counts, dp->part_g, dp->part_r);
   const bool use_given = norm && norm->use_given;
-  launch_norm_scan(s, dp->tile_counts, dp->ntiles, dp->tile_offsets, dp->tile_slot, dp->part_g, SL.nblk_g, dp->part_r,
+  // (buffer A is free until the x pass)
+  const PaintCut cut = paint_cut(h.N, gal->n + ran->n, dp->bufA, spectrum_buffer_bytes(h));
+  launch_norm_scan(s, dp->tile_counts, dp->ntiles, dp->tile_offsets, dp->tile_slot, cut, dp->part_g, SL.nblk_g, dp->part_r,
                    SL.nblk_r, dp->norm, cfg->box_origin, cfg->box_len, h.check_extent, use_given ? 1 : 0,
                    use_given ? norm->alpha_r : 0.0, use_given ? norm->I : 0.0, use_given ? norm->S : 0.0);
   launch_sort_scatter(s, SL, gx, gal->dtype, rx, ran->dtype, gal->n, ran->n, h.prec, h.N, cfg->box_origin, h.H,
                       cfg->assign, dp->norm, chunk_hist, dp->tile_offsets, records);
   auto paint = [&](ColTune t) {
-    // (buffer A is free until the x pass)
-    launch_tile_paint(s, h.prec, h.N, cfg->assign, gal->n + ran->n, dp->tile_offsets, dp->tile_slot, records, dp->norm,
-                      dp->tile_blocks, dp->bufA, spectrum_buffer_bytes(h), t);
+    launch_tile_paint(s, h.prec, h.N, cfg->assign, dp->tile_offsets, dp->tile_slot, records, dp->norm,
+                      dp->tile_blocks, cut, t);
   };
   auto gather = [&](ColTune t) {
     launch_tile_gather(s, h.prec, h.N, dp->tile_slot, dp->tile_blocks, dp->mesh, dp->rowmask, t);

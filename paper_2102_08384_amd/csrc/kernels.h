@@ -105,11 +105,24 @@ SortLayout sort_layout(int N, int64_t n_gal, int64_t n_ran);
 void launch_sort_count(hipStream_t s, const SortLayout &L, const void *gx, int gdtype, const void *rx, int rdtype,
                        const void *rnbar, int64_t ng, int64_t nr, int N, const double *b0, double H, int assign,
                        int *chunk_hist, int *counts, double *part_g, double *part_r);
+// Tiles painted by several workgroups.  `mem` (memory that is free during the paint) holds, written by the
+// scan, the numbers of whole tiles and of parts and a list of both, the whole tiles first: the tile's slot,
+// its first part's index among the parts, its first record and its records; behind the list an int64 block
+// for each part.  per: records of a part (0: every tile by one workgroup, no list); most: parts at most.
+struct PaintCut {
+  static constexpr int kMost = 1024;
+  int per = 0, most = 0, list_bytes = 0;
+  void *mem = nullptr;
+  __device__ int *head() const { return (int *)mem; }
+  __device__ int4 *entry() const { return (int4 *)((char *)mem + 256); }
+  __device__ long long *blocks() const { return (long long *)((char *)mem + list_bytes); }
+};
+PaintCut paint_cut(int N, int64_t n_part, void *scratch, size_t scratch_bytes);
 // After pass 1, in one launch: offsets and slot (exclusive scan of the tile counts, compact slots of the
 // occupied tiles), and alpha_r, I, S, the range / extent flags and the painting scale from the
 // partial rows of the two catalogs (nblk_g, nblk_r rows of kScalarCols).
-void launch_norm_scan(hipStream_t s, const int *counts, int ntiles, int *offsets, int *slot, const double *pg,
-                      int nblk_g, const double *pr, int nblk_r, DevNorm *norm, const double *b0, double L,
+void launch_norm_scan(hipStream_t s, const int *counts, int ntiles, int *offsets, int *slot, const PaintCut &cut,
+                      const double *pg, int nblk_g, const double *pr, int nblk_r, DevNorm *norm, const double *b0, double L,
                       int check_extent, int use_given, double ga, double gI, double gS);
 // Pass 2: tile-sorted records in the mesh precision (prec), randoms weighted by -alpha_r.
 // chunk_hist's counts become run bases in place (offsets: the tile offsets of the scan).
@@ -118,10 +131,8 @@ void launch_sort_scatter(hipStream_t s, const SortLayout &L, const void *gx, int
                          int assign, const DevNorm *norm, int *chunk_hist, const int *offsets, void *records);
 // blocks: scratch of ntiles * (TS+2)^3 values of the mesh precision, one block per occupied tile
 // (slot: [ntiles + 1] from the scan).
-// scratch (free memory during the paint): the parts' blocks of tiles that several workgroups share;
-// n_part: the particles of both catalogs.
-void launch_tile_paint(hipStream_t s, int prec, int N, int assign, int64_t n_part, const int *offsets, const int *slot,
-                       const void *records, const DevNorm *norm, void *blocks, void *scratch, size_t scratch_bytes,
+void launch_tile_paint(hipStream_t s, int prec, int N, int assign, const int *offsets, const int *slot,
+                       const void *records, const DevNorm *norm, void *blocks, const PaintCut &cut,
                        ColTune tune = ColTune());
 // Every mesh node = the sum of the blocks covering it.  rowmask (N*N ints, zeroed by the
 // caller; may be null) receives 1 for every x-row (z, y) holding a non-zero node.

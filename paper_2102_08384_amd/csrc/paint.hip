@@ -279,14 +279,22 @@ k_sort_count(const RG *__restrict__ gx, const RR *__restrict__ rx, const RR *__r
   }
 }
 
+// parts of a tile of `len` records: `per` records each, kTileParts at most (per 0: whole tiles)
+constexpr int kTileParts = 16;
+__device__ __forceinline__ int tile_parts(int len, int per) {
+  return (per > 0 && len > per) ? min((len + per - 1) / per, kTileParts) : 1;
+}
+
 // offsets = exclusive scan of counts (offsets[ntiles] = total),
 // slot[t] = rank of tile t among the occupied tiles (-1 if empty), slots[ntiles] = count.
 // Thread i owns the run [i * per, (i + 1) * per); when ntiles is a multiple of 4 * 1024 (and
 // per <= 64) the runs are read and written as 16-byte vectors.
+// cut.per > 0: also the list of whole tiles and parts to paint (see PaintCut).
 __device__ void tile_scan(const int *__restrict__ counts, int ntiles, int *__restrict__ offsets,
-                          int *__restrict__ slot) {
+                          int *__restrict__ slot, const PaintCut cut) {
   __shared__ int part[1024];
   __shared__ int occ[1024];
+  __shared__ int lst[1024];
   const int per = (ntiles + 1023) / 1024;
   const int b = threadIdx.x * per, e = min(ntiles, b + per);
   const bool vec = (ntiles % 4096) == 0 && per <= 64;
@@ -309,15 +317,28 @@ __device__ void tile_scan(const int *__restrict__ counts, int ntiles, int *__res
       o += counts[i] > 0;
     }
   }
+  // (tiles are cut on meshes of 1, 8, 64, 512 or 4096 tiles: runs of one tile, or vectors of four)
+  const int len[4] = {vec ? c[0] : s, vec ? c[1] : 0, vec ? c[2] : 0, vec ? c[3] : 0};
+  int np[4] = {0, 0, 0, 0}, l = 0;  // l: parts of this run's cut tiles, and from bit 16 the number of those tiles
+  if (cut.per > 0) {  // uniform
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      np[k] = tile_parts(len[k], cut.per);
+      if (np[k] > 1) l += np[k] + 0x10000;
+    }
+  }
   part[threadIdx.x] = s;
   occ[threadIdx.x] = o;
+  lst[threadIdx.x] = l;
   __syncthreads();
   for (int off = 1; off < 1024; off <<= 1) {  // inclusive Hillis-Steele scans
     int v = (int)threadIdx.x >= off ? part[threadIdx.x - off] : 0;
     int w = (int)threadIdx.x >= off ? occ[threadIdx.x - off] : 0;
+    int u = (int)threadIdx.x >= off ? lst[threadIdx.x - off] : 0;
     __syncthreads();
     part[threadIdx.x] += v;
     occ[threadIdx.x] += w;
+    lst[threadIdx.x] += u;
     __syncthreads();
   }
   int run = threadIdx.x > 0 ? part[threadIdx.x - 1] : 0;
@@ -346,15 +367,37 @@ __device__ void tile_scan(const int *__restrict__ counts, int ntiles, int *__res
     offsets[ntiles] = part[1023];
     slot[ntiles] = occ[1023];
   }
+  if (cut.per > 0) {
+    const int before = threadIdx.x > 0 ? lst[threadIdx.x - 1] : 0;
+    const int whole = occ[1023] - (lst[1023] >> 16);
+    int beg = threadIdx.x > 0 ? part[threadIdx.x - 1] : 0, rank = threadIdx.x > 0 ? occ[threadIdx.x - 1] : 0;
+    int w = rank - (before >> 16), first = before & 0xffff;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (len[k] == 0) continue;
+      if (np[k] > 1) {
+        for (int n = 0; n < np[k]; ++n) cut.entry()[whole + first + n] = make_int4(rank, first, beg, len[k]);
+        first += np[k];
+      } else {
+        cut.entry()[w++] = make_int4(rank, 0, beg, len[k]);
+      }
+      beg += len[k];
+      ++rank;
+    }
+    if (threadIdx.x == 1023) {
+      cut.head()[0] = whole;
+      cut.head()[1] = lst[1023] & 0xffff;
+    }
+  }
 }
 
 // Both need only k_sort_count's results and each is one workgroup's latency: workgroup 0 scans,
 // workgroup 1 folds the scalars meanwhile.  At 512^3 19.7 us, against 18.8 + 10.1 one after the other.
 __global__ void __launch_bounds__(1024) k_norm_scan(const int *counts, int ntiles, int *offsets, int *slot,
-                                                    const double *pg, int nblk_g, const double *pr, int nblk_r,
+                                                    const PaintCut cut, const double *pg, int nblk_g, const double *pr, int nblk_r,
                                                     DevNorm *norm, double b0x, double b0y, double b0z, double L,
                                                     int check_extent, int use_given, double ga, double gI, double gS) {
-  if (blockIdx.x == 0) tile_scan(counts, ntiles, offsets, slot);
+  if (blockIdx.x == 0) tile_scan(counts, ntiles, offsets, slot, cut);
   else finalize_norm(pg, nblk_g, pr, nblk_r, norm, b0x, b0y, b0z, L, check_extent, use_given, ga, gI, gS);
 }
 
@@ -454,35 +497,34 @@ k_sort_scatter(const RG *__restrict__ gx, const RR *__restrict__ rx, int64_t ng,
 // the bit pattern minus that of 1.5 * 2^52 is the rounded integer in two's complement): three
 // operations in place of the dozen of a general float-to-int64 conversion.  The quantum, 2^-50
 // of the catalog's total |weight|, stays far below FP32 resolution.
-// Where few tiles hold the catalog (64^3 has 64 in all; a survey in a doubled 256^3 box fills about
-// 150) a workgroup per tile leaves most CUs idle, so a tile is cut into up to gridDim.y parts, a
-// workgroup each, which leave their int64 blocks in `parts`; k_tile_combine adds them (exact, so the
-// split does not show in the mesh).  A part holds at least 2048 records (zeroing and storing a block
-// cost about as much as depositing 1000) and a 512th of the catalog (two workgroups per CU in all:
-// with a 2048-record limit alone, 10^3 occupied tiles of 6 10^3 records were cut in three and the
-// stage went from 0.40 to 0.50 ms).  `parts` has room for `room` blocks, shared evenly by the occupied
-// tiles.  Eight catalogs of 6 10^5 particles on 64^3: 2.09 -> 1.4 ms for the whole batch; 6 10^6 on a
-// doubled 256^3 box: paint stage 0.56 -> 0.43 ms.
-struct PartShare {
-  int per, most;  // records of a part; parts of a tile at most
-};
-__device__ __forceinline__ PartShare part_share(const int *offsets, const int *slot, int ntiles, int most, int room) {
-  const int occ = slot[ntiles];
-  return PartShare{max(2048, offsets[ntiles] / 512), max(1, min(most, room / max(occ, 1)))};
-}
-__device__ __forceinline__ int tile_parts(int len, PartShare sh) { return min((len + sh.per - 1) / sh.per, sh.most); }
+// (a value that every lane holds, in a scalar register)
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
+// cut.per > 0: the workgroups take the listed whole tiles and then the listed parts of the crowded ones,
+// which leave int64 blocks for k_tile_combine (see PaintCut).  The list holds the work without gaps, the
+// larger pieces first: with 512 tiles at 128^3, half of them cut in two, the paint stage takes 0.151 ms; with
+// a workgroup for every tile and the list of parts beside them, 0.157 (a CU then gets two whole tiles or none).
 template <typename RM, int ASSIGN>
 __global__ void __launch_bounds__(512) k_tile_paint(int ts, const int *__restrict__ offsets,
                                                     const int *__restrict__ slot,
                                                     const typename Rec4<RM>::T *__restrict__ rec,
                                                     const DevNorm *__restrict__ norm, RM *__restrict__ blocks,
-                                                    long long *__restrict__ parts, int room) {
-  const int tile = blockIdx.x;
-  const PartShare sh = part_share(offsets, slot, gridDim.x, gridDim.y, room);
-  const int beg0 = offsets[tile], len = offsets[tile + 1] - beg0;
-  const int np = tile_parts(len, sh), part = blockIdx.y;
-  if (part >= np) return;  // uniform for the block (len 0: no parts)
+                                                    const PaintCut cut) {
+  int beg0, len, at, part = 0, np = 1, whole = 0;
+  if (cut.per > 0) {  // uniform, as all below
+    const int4 e = cut.entry()[blockIdx.x];  // (loaded beside the counts: the list has room for every workgroup's)
+    whole = uniform(cut.head()[0]);
+    if ((int)blockIdx.x >= whole + uniform(cut.head()[1])) return;
+    at = uniform(e.x); beg0 = uniform(e.z); len = uniform(e.w);
+    np = tile_parts(len, cut.per);
+    if (np > 1) part = (int)blockIdx.x - whole - uniform(e.y);
+  } else {
+    const int tile = blockIdx.x;
+    beg0 = offsets[tile];
+    len = offsets[tile + 1] - beg0;
+    at = slot[tile];
+    if (len == 0) return;
+  }
   const int beg = beg0 + (int)((int64_t)len * part / np), end = beg0 + (int)((int64_t)len * (part + 1) / np);
   extern __shared__ __align__(16) unsigned char smem_raw[];
   unsigned long long *acc = reinterpret_cast<unsigned long long *>(smem_raw);
@@ -540,32 +582,31 @@ __global__ void __launch_bounds__(512) k_tile_paint(int ts, const int *__restric
   }
   __syncthreads();
   if (np > 1) {
-    long long *dst = parts + ((size_t)slot[tile] * sh.most + part) * E3;
+    long long *dst = cut.blocks() + (size_t)((int)blockIdx.x - whole) * E3;
     for (int c = threadIdx.x; c < E3; c += blockDim.x) dst[c] = (long long)acc[c];
     return;
   }
   const double inv = 1.0 / qscale;
-  RM *dst = blocks + (size_t)slot[tile] * E3;
+  RM *dst = blocks + (size_t)at * E3;
   for (int c = threadIdx.x; c < E3; c += blockDim.x) dst[c] = (RM)((double)(long long)acc[c] * inv);
 }
 
-// Tiles painted in parts (`most`: the paint's gridDim.y): the sum of their int64 blocks, converted as
-// k_tile_paint converts a whole tile's.
+// Tiles painted in parts: the sum of their int64 blocks, converted as k_tile_paint converts a whole
+// tile's.  The workgroups of a tile's list entries share out its cells.
 template <typename RM>
-__global__ void __launch_bounds__(256) k_tile_combine(int ts, int most, const int *__restrict__ offsets,
-                                                      const int *__restrict__ slot, const DevNorm *__restrict__ norm,
-                                                      const long long *__restrict__ parts, int room,
+__global__ void __launch_bounds__(256) k_tile_combine(int ts, const DevNorm *__restrict__ norm, const PaintCut cut,
                                                       RM *__restrict__ blocks) {
-  const int tile = blockIdx.x;
-  const PartShare sh = part_share(offsets, slot, gridDim.x, most, room);
-  const int np = tile_parts(offsets[tile + 1] - offsets[tile], sh);
-  if (np < 2) return;  // uniform
+  if ((int)blockIdx.x >= cut.head()[1]) return;  // uniform
+  const int4 e = cut.entry()[cut.head()[0] + blockIdx.x];
+  const int np = tile_parts(e.w, cut.per);
   const int E = ts + 2, E3 = E * E * E;
   const double inv = 1.0 / (sizeof(RM) == 4 ? norm->fix_scale * (1.0 / 2048.0) : norm->fix_scale);
-  const long long *src = parts + (size_t)slot[tile] * sh.most * E3;
-  RM *dst = blocks + (size_t)slot[tile] * E3;
-  for (int c = blockIdx.y * blockDim.x + threadIdx.x; c < E3; c += gridDim.y * blockDim.x) {
+  const long long *src = cut.blocks() + (size_t)e.y * E3;
+  RM *dst = blocks + (size_t)e.x * E3;
+  const int share = ((int)blockIdx.x - e.y) * gridDim.y + blockIdx.y;
+  for (int c = share * blockDim.x + threadIdx.x; c < E3; c += np * gridDim.y * blockDim.x) {
     long long v = 0;
+#pragma unroll 4
     for (int i = 0; i < np; ++i) v += src[(size_t)i * E3 + c];
     dst[c] = (RM)((double)v * inv);
   }
@@ -863,10 +904,10 @@ void launch_sort_scatter(hipStream_t s, const SortLayout &L, const void *gx, int
 #undef PW_SS
 }
 
-void launch_norm_scan(hipStream_t s, const int *counts, int ntiles, int *offsets, int *slot, const double *pg,
-                      int nblk_g, const double *pr, int nblk_r, DevNorm *norm, const double *b0, double L,
+void launch_norm_scan(hipStream_t s, const int *counts, int ntiles, int *offsets, int *slot, const PaintCut &cut,
+                      const double *pg, int nblk_g, const double *pr, int nblk_r, DevNorm *norm, const double *b0, double L,
                       int check_extent, int use_given, double ga, double gI, double gS) {
-  hipLaunchKernelGGL(k_norm_scan, dim3(2), dim3(1024), 0, s, counts, ntiles, offsets, slot, pg, nblk_g, pr, nblk_r, norm,
+  hipLaunchKernelGGL(k_norm_scan, dim3(2), dim3(1024), 0, s, counts, ntiles, offsets, slot, cut, pg, nblk_g, pr, nblk_r, norm,
                      b0[0], b0[1], b0[2], L, check_extent, use_given, ga, gI, gS);
 }
 
@@ -876,35 +917,52 @@ static int ilog2(int v) {
   return r;
 }
 
-// Parts of a tile at most: 1 (no second launch) on meshes whose tiles outnumber the CUs many times, for
-// catalogs too thin to fill parts (128^3, 3.6 10^5 particles, whole estimates: 170 us whole tiles, 178
-// in parts; 1.65 10^6: 290 and 279).
-static int paint_parts(int64_t ntiles, int64_t n_part, int64_t room) {
-  if (ntiles > 4096 || n_part < kSortNominalCUs * 1024 || n_part < ntiles * (ntiles > 512 ? 256 : 1024)) return 1;
-  if (room < 2) return 1;
-  return ntiles > 512 ? 8 : 16;  // (workgroups without a part still have to be started)
+// Where few tiles hold the catalog (64^3 has 64 in all; a survey in a doubled 256^3 box fills about
+// 150) a workgroup per tile leaves most CUs idle, so crowded tiles are cut into parts, a workgroup each,
+// which leave their int64 blocks behind the list of parts in `scratch`; k_tile_combine adds them (exact,
+// so the cut does not show in the mesh).  A part holds at least 2048 records (zeroing and storing a block
+// cost about as much as depositing 1000) and a 512th of the catalog (two workgroups per CU in all:
+// with a 2048-record limit alone, 10^3 occupied tiles of 6 10^3 records were cut in three and the
+// stage went from 0.40 to 0.50 ms).  So there are at most 2 n / per parts: fewer than n / per tiles
+// hold more than `per`, and each adds one to its share of n / per.  Paint stage, whole tiles -> this: 6 10^6
+// particles of a survey in a doubled 256^3 box 0.52 -> 0.25 ms, 1.5 10^6 at 128^3 0.148 -> 0.113 ms.
+// Whole tiles on meshes whose tiles outnumber the CUs many times, and for catalogs too thin to fill
+// parts (128^3, 3.6 10^5 particles, whole estimates: 170 us whole tiles, 178 in parts; 1.65 10^6: 290 and
+// 279).  The work comes from a list, so where no tile is crowded only the list and some empty workgroups are
+// added: 6 10^6 particles evenly in a 256^3 box 0.336 -> 0.345 ms (a grid of tiles times parts: 0.37 ms).
+PaintCut paint_cut(int N, int64_t n_part, void *scratch, size_t scratch_bytes) {
+  PaintCut cut;
+  const int ts = tile_size(N);
+  const int64_t nt = N / ts, ntiles = nt * nt * nt;
+  if (ntiles > 4096 || n_part < kSortNominalCUs * 1024 || n_part < ntiles * (ntiles > 512 ? 256 : 1024)) return cut;
+  const size_t E3 = (size_t)(ts + 2) * (ts + 2) * (ts + 2);
+  const int64_t list = (256 + (ntiles + PaintCut::kMost) * (int64_t)sizeof(int4) + 255) / 256 * 256;
+  const int64_t room = ((int64_t)scratch_bytes - list) / (int64_t)(E3 * sizeof(long long));
+  const int64_t n = std::min({(int64_t)PaintCut::kMost / 2, n_part / 2048, room / 2});
+  if (n < 32) return cut;  // (no room for parts small enough to matter)
+  cut.per = (int)std::max<int64_t>(2048, (n_part + n - 1) / n);
+  cut.most = (int)(2 * n);
+  cut.list_bytes = (int)list;
+  cut.mem = scratch;
+  return cut;
 }
 
-void launch_tile_paint(hipStream_t s, int prec, int N, int assign, int64_t n_part, const int *offsets, const int *slot,
-                       const void *records, const DevNorm *norm, void *blocks, void *scratch, size_t scratch_bytes,
-                       ColTune tune) {
+void launch_tile_paint(hipStream_t s, int prec, int N, int assign, const int *offsets, const int *slot,
+                       const void *records, const DevNorm *norm, void *blocks, const PaintCut &cut, ColTune tune) {
   const int ts = tile_size(N);
   const int nt = N / ts;
   const unsigned ntiles = (unsigned)(nt * nt * nt);
   const size_t E3 = (size_t)(ts + 2) * (ts + 2) * (ts + 2);
   const int threads = (tune.threads == 128 || tune.threads == 512) ? tune.threads : 256;
-  const int room = (int)std::min<size_t>(scratch_bytes / (E3 * sizeof(long long)), 1u << 30);
-  const int most = paint_parts(ntiles, n_part, room);
 #define PW_TP(RM, A)                                                                              \
-  hipLaunchKernelGGL((k_tile_paint<RM, A>), dim3(ntiles, most), dim3(threads), E3 * sizeof(unsigned long long), s, \
-                     ts, offsets, slot, (const typename Rec4<RM>::T *)records, norm, (RM *)blocks, (long long *)scratch, room)
+  hipLaunchKernelGGL((k_tile_paint<RM, A>), dim3(ntiles + cut.most), dim3(threads), E3 * sizeof(unsigned long long), s, \
+                     ts, offsets, slot, (const typename Rec4<RM>::T *)records, norm, (RM *)blocks, cut)
   if (prec == 0) { if (assign == 2) PW_TP(float, 2); else PW_TP(float, 3); }
   else { if (assign == 2) PW_TP(double, 2); else PW_TP(double, 3); }
 #undef PW_TP
-  if (most < 2) return;
+  if (cut.per == 0) return;
 #define PW_TC(RM)                                                                                             \
-  hipLaunchKernelGGL(k_tile_combine<RM>, dim3(ntiles, ntiles > 512 ? 3 : 12), dim3(256), 0, s, ts, most, offsets, slot, norm,       \
-                     (const long long *)scratch, room, (RM *)blocks)
+  hipLaunchKernelGGL(k_tile_combine<RM>, dim3(cut.most, 4), dim3(256), 0, s, ts, norm, cut, (RM *)blocks)
   if (prec == 0) PW_TC(float);
   else PW_TC(double);
 #undef PW_TC
