@@ -209,16 +209,22 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void *p, uint32
 // (kNt, the streaming policy), and so do the stores of a stack of fields that no cache holds
 // until the next pass (keep_lines).  Whole estimates, policy off -> on: 128^3 0.554 -> 0.497 ms,
 // 512^3 bisector P_l 8.79 -> 8.54 ms; at 64^3, where a stack fits the 256 MB Infinity Cache, streaming
-// stores cost the next pass its hits (inverse x pass 30 -> 42 us), so they keep the default there.
+// stores cost the next pass its hits (inverse x pass 30 -> 42 us), so they keep the default there.  So
+// do FP32 loads (keep_loads): midpoint P_l at 64^3, y pass 24.2 -> 18.7 us and fused z pass 46.0 -> 43.3 us
+// without streaming.  FP64 stacks are twice as large: the same passes 28.8 -> 28.1 and 64.6 -> 69.5 us,
+// midpoint xi_l's y pass 49 -> 64 us, so FP64 loads stream on every mesh.
 constexpr int kNt = 2;
 __host__ __device__ constexpr bool keep_lines(int N) { return N < 128; }
-template <typename R>
+__host__ __device__ constexpr int store_policy(int N) { return keep_lines(N) ? 0 : kNt; }
+template <typename R> __host__ __device__ constexpr bool keep_loads(int N) { return sizeof(R) == 4 && keep_lines(N); }
+template <typename R> __host__ __device__ constexpr int load_policy(int N) { return keep_loads<R>(N) ? 0 : kNt; }
+template <typename R, int POLICY>
 __device__ __forceinline__ cplx<R> buf_load(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
   if constexpr (sizeof(R) == 4) {
-    const f32x2 v = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, kNt));
+    const f32x2 v = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, POLICY));
     return mk<R>(v.x, v.y);
   } else {
-    const f64x2 v = __builtin_bit_cast(f64x2, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, kNt));
+    const f64x2 v = __builtin_bit_cast(f64x2, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, POLICY));
     return mk<R>(v.x, v.y);
   }
 }
@@ -260,9 +266,11 @@ __device__ __forceinline__ cplx<R> lane_fetch(int src, cplx<R> v) {
 }
 
 // The same policy for plain accesses (NT false: the default policy)
-template <typename C> __device__ __forceinline__ C load_nt(const C *p) {
+template <bool NT, typename C> __device__ __forceinline__ C load_nt(const C *p) {
   C x;
-  if constexpr (sizeof(C) == 8) {
+  if constexpr (!NT) {
+    x = *p;
+  } else if constexpr (sizeof(C) == 8) {
     const f32x2 v = __builtin_nontemporal_load(reinterpret_cast<const f32x2 *>(p));
     x.x = v.x; x.y = v.y;
   } else {
@@ -270,6 +278,11 @@ template <typename C> __device__ __forceinline__ C load_nt(const C *p) {
     x.x = v.x; x.y = v.y;
   }
   return x;
+}
+
+template <bool NT, typename R> __device__ __forceinline__ R load_real_nt(const R *p) {
+  if constexpr (NT) return __builtin_nontemporal_load(p);
+  else return *p;
 }
 
 template <bool NT, typename C> __device__ __forceinline__ void store_nt(C *p, C x) {

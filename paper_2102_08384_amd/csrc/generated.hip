@@ -58,7 +58,7 @@ k_contract_bis_reg(const cplx<R> *__restrict__ spec, int64_t nmodes, int64_t mst
     if (b < 0) continue;
     cplx<R> a[NF];
 #pragma unroll
-    for (int p = 0; p < NF; ++p) a[p] = load_nt(spec + (size_t)p * mstride + mode);
+    for (int p = 0; p < NF; ++p) a[p] = load_nt<true>(spec + (size_t)p * mstride + mode);
     const bool pair = (kx != 0 && kx != half);
     R wdir[NSH];
 #pragma unroll
@@ -189,7 +189,7 @@ k_targets(const cplx<R> *__restrict__ spec, int64_t nmodes, int64_t mstride, int
        i += (int64_t)gridDim.x * blockDim.x) {
     cplx<R> a[NF];
 #pragma unroll
-    for (int p = 0; p < NF; ++p) a[p] = load_nt(spec + (size_t)p * mstride + i);
+    for (int p = 0; p < NF; ++p) a[p] = load_nt<true>(spec + (size_t)p * mstride + i);
     R full[NSH];
     CT::targets(a, full);
     R iw2 = (R)1;

@@ -85,8 +85,8 @@ k_iz(const R *__restrict__ in, cplx<R> *__restrict__ out, int nfields, int64_t n
     const R *src = mine + (size_t)p * fstride;
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
-      xa[s] = __builtin_nontemporal_load(src + s * T * C);
-      xb[s] = p + 1 < nfields ? __builtin_nontemporal_load(src + fstride + s * T * C) : (R)0;
+      xa[s] = load_real_nt<!keep_loads<R>(N)>(src + s * T * C);
+      xb[s] = p + 1 < nfields ? load_real_nt<!keep_loads<R>(N)>(src + fstride + s * T * C) : (R)0;
     }
   };
   fetch(0);
@@ -198,7 +198,7 @@ k_fziz(const cplx<R> *__restrict__ in, R *__restrict__ prod, const SphereSet sph
   auto load = [&](int p, cplx<R> *v) {
     const __amdgpu_buffer_rsrc_t r = buf_rsrc(in + (size_t)p * N * npen, in_bytes);
 #pragma unroll
-    for (int s = 0; s < 8; ++s) v[s] = (wload >> s & 1) ? buf_load<R>(r, lo[s], (uint32_t)s * sT) : mk<R>(0, 0);
+    for (int s = 0; s < 8; ++s) v[s] = (wload >> s & 1) ? buf_load<R, load_policy<R>(N)>(r, lo[s], (uint32_t)s * sT) : mk<R>(0, 0);
   };
   auto at = [c](int i) -> cplx<R> & { return lds[i * (C + 1) + c]; };
   auto sync = []() { __syncthreads(); };
@@ -224,7 +224,7 @@ k_fziz(const cplx<R> *__restrict__ in, R *__restrict__ prod, const SphereSet sph
       const __amdgpu_buffer_rsrc_t r = buf_rsrc(out + (size_t)(p - n_inplace) * nz * npen, out_bytes);
 #pragma unroll
       for (int s = 0; s < 8; ++s)
-        if (wstore >> s & 1) buf_store<R, keep_lines(N) ? 0 : kNt>(v[s], r, zo[s], 0);
+        if (wstore >> s & 1) buf_store<R, store_policy(N)>(v[s], r, zo[s], 0);
     }
   };
   // conj(D) / W^2 on every mode, D = d_scale Q_000~; field 0's own product is then
@@ -331,7 +331,7 @@ k_fziz_half(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, int nfiel
   auto load = [&](int p, cplx<R> *v) {
     const __amdgpu_buffer_rsrc_t r = buf_rsrc(in + (size_t)p * N * npen, in_bytes);
 #pragma unroll
-    for (int s = 0; s < 8; ++s) v[s] = (wload >> s & 1) ? buf_load<R>(r, lo[s], (uint32_t)s * sT) : mk<R>(0, 0);
+    for (int s = 0; s < 8; ++s) v[s] = (wload >> s & 1) ? buf_load<R, load_policy<R>(N)>(r, lo[s], (uint32_t)s * sT) : mk<R>(0, 0);
   };
   auto at = [c](int i) -> cplx<R> & { return lds[i * (C + 1) + c]; };
   auto sync = []() { __syncthreads(); };
@@ -381,8 +381,8 @@ k_fziz_half(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, int nfiel
     const __amdgpu_buffer_rsrc_t rb = buf_rsrc(out + (size_t)(p + 1) * nz * npen, out_bytes);
     split_half<R, T, N>(v, t, nz - 1, at, [&](int, int z, cplx<R> ha, cplx<R> hb) {
       const uint32_t zo = has ? (uint32_t)((z * npen + q) * E) : kOob;
-      buf_store<R, keep_lines(N) ? 0 : kNt>(odd_a ? mk<R>(-ha.y, ha.x) : ha, ra, zo, 0);
-      if (two) buf_store<R, keep_lines(N) ? 0 : kNt>(odd_b ? mk<R>(-hb.y, hb.x) : hb, rb, zo, 0);
+      buf_store<R, store_policy(N)>(odd_a ? mk<R>(-ha.y, ha.x) : ha, ra, zo, 0);
+      if (two) buf_store<R, store_policy(N)>(odd_b ? mk<R>(-hb.y, hb.x) : hb, rb, zo, 0);
     });
   }
 }
@@ -457,11 +457,11 @@ k_iy_half(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, R *__restri
     const uint32_t lo = cb * C + c < nkx ? lane : kOob;
     const __amdgpu_buffer_rsrc_t ra = buf_rsrc(in + ((size_t)p * N + z) * plane + cb * C, bytes);
 #pragma unroll
-    for (int s = 0; s < 8; ++s) a[s] = buf_load<R>(ra, lo, (uint32_t)s * sT);
+    for (int s = 0; s < 8; ++s) a[s] = buf_load<R, load_policy<R>(N)>(ra, lo, (uint32_t)s * sT);
     if (!self) {
       const __amdgpu_buffer_rsrc_t rb = buf_rsrc(in + ((size_t)p * N + zm) * plane + cb * C, bytes);
 #pragma unroll
-      for (int s = 0; s < 8; ++s) b[s] = buf_load<R>(rb, lo, (uint32_t)s * sT);
+      for (int s = 0; s < 8; ++s) b[s] = buf_load<R, load_policy<R>(N)>(rb, lo, (uint32_t)s * sT);
     }
   };
   int lb = 0;
@@ -511,7 +511,7 @@ k_iy_half(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, R *__restri
     fft_pencil_db<R, N, true>(v, t, twr, at, sync, flip);
     const __amdgpu_buffer_rsrc_t w = buf_rsrc(out + ((size_t)pc * NZ + z) * plane + cbc * C, bytes);
 #pragma unroll
-    for (int s = 0; s < 8; ++s) buf_store<R, keep_lines(N) ? 0 : kNt>(v[s], w, lane, (uint32_t)s * sT);
+    for (int s = 0; s < 8; ++s) buf_store<R, store_policy(N)>(v[s], w, lane, (uint32_t)s * sT);
     if (!self) {
       // (the transform's barriers lie between every wave's row of red and this read, and the next
       // item's between this read and that row's next write: two rows alternate)

@@ -401,7 +401,7 @@ k_fy(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, int nfields, int
     const __amdgpu_buffer_rsrc_t r = buf_rsrc(in + ((size_t)p * nplanes + z) * plane + cb * C, in_bytes);
 #pragma unroll
     for (int s = 0; s < 8; ++s)
-      v[s] = ((wlive >> s) & 1u) ? buf_load<R>(r, colok ? lo[s] : kOob, (uint32_t)s * sT) : mk<R>(0, 0);
+      v[s] = ((wlive >> s) & 1u) ? buf_load<R, load_policy<R>(N)>(r, colok ? lo[s] : kOob, (uint32_t)s * sT) : mk<R>(0, 0);
   };
   int lb = 0;
   auto at = [c, &lb](int i) -> cplx<R> & { return lds[lb * LB + i * (C + 1) + c]; };
@@ -427,7 +427,7 @@ k_fy(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, int nfields, int
     for (int s = 0; s < 8; ++s) {
       // whole 128-byte lines: the row's padding slots are written too (never read as modes)
       const bool keep = kx < yl[s];
-      if (__builtin_amdgcn_ballot_w64(keep)) buf_store<R, keep_lines(N) ? 0 : kNt>(v[s], w, keep ? so[s] : kOob, 0);
+      if (__builtin_amdgcn_ballot_w64(keep)) buf_store<R, store_policy(N)>(v[s], w, keep ? so[s] : kOob, 0);
     }
   }
 }
@@ -537,7 +537,7 @@ k_fz(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, int nfields, int
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
       const int z = t + s * T;
-      v[s] = (has && msk[z]) ? load_nt(src + (size_t)z * npen + q) : mk<R>(0, 0);
+      v[s] = (has && msk[z]) ? load_nt<!keep_loads<R>(N)>(src + (size_t)z * npen + q) : mk<R>(0, 0);
     }
   };
   int lb = 0;

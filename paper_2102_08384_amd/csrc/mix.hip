@@ -81,8 +81,8 @@ k_mix(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, int rs, int nkx
     const cplx<R> *pa = in + (size_t)f * fin + row * rs, *pb = pa + fin;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      ha[s] = f < NG ? load_nt(pa + t + s * T) : mk<R>(0, 0);
-      hb[s] = f + 1 < NG ? load_nt(pb + t + s * T) : mk<R>(0, 0);
+      ha[s] = f < NG ? load_nt<!keep_loads<R>(N)>(pa + t + s * T) : mk<R>(0, 0);
+      hb[s] = f + 1 < NG ? load_nt<!keep_loads<R>(N)>(pb + t + s * T) : mk<R>(0, 0);
     }
     if (t == 0) {
       na = f < NG ? pa[N / 2].x : (R)0;
