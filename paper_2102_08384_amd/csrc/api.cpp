@@ -1027,7 +1027,9 @@ DevPlan *launch_estimate(pw_ctx *ctx, Lane &ln, const pw_config *cfg, const pw_c
     const int nzr = h.mid_half ? N / 2 + 1 : npl;  // planes it leaves
     const double yrows = (double)h.n_inv * nzr * h.ny * F.nkx * csz;
     mark("iy", (double)h.n_inv * npl * N * F.nkx * csz + yrows);
-    tuned_launch(ctx, ln, tune_key("iy", h, h.n_inv, npl, h.ny), fy_candidates(h.prec, h.n_inv), [&](ColTune t) {
+    // (launch_iy_half has one column shape, as FP64 has: the field groupings alone)
+    const auto ycand = fy_candidates(h.mid_half ? PW_FP64 : h.prec, h.n_inv);
+    tuned_launch(ctx, ln, tune_key("iy", h, h.n_inv, npl, h.ny), ycand, [&](ColTune t) {
       if (h.mid_half)
         launch_iy_half(s, h.prec, N, zout, yout, B + hl.nyx, B + hl.nyy, h.n_inv, F.nkx, F.rs, dp->odd_of, dp->tw, t);
       else
