@@ -375,30 +375,6 @@ template <typename R> __device__ __forceinline__ R sh_n(const ShConst &c, int l,
 template <> __device__ __forceinline__ float sh_n<float>(const ShConst &c, int l, int m) { return c.nrm[l][m]; }
 template <> __device__ __forceinline__ double sh_n<double>(const ShConst &c, int l, int m) { return c.nrm_d[l][m]; }
 
-// y_J^{m} and y_J^{-m} (m >= 0; for m == 0 only *ym is meaningful) of the unit vector (x,y,z).
-template <typename R>
-__device__ __forceinline__ void real_sh_pair(const ShConst &c, int J, int m, R x, R y, R z, R *yp, R *ym) {
-  // (x + i y)^m
-  R cr = 1, ci = 0;
-  for (int i = 0; i < m; ++i) {
-    R t = cr * x - ci * y;
-    ci = cr * y + ci * x;
-    cr = t;
-  }
-  R q0 = 1, q1 = 0;  // Qt_{l-1}, Qt_{l-2}
-  if (J > m) {
-    R qa = (R)(2 * m + 1) * z;
-    q1 = q0; q0 = qa;
-    for (int l = m + 2; l <= J; ++l) {
-      R qn = sh_a<R>(c, l, m) * z * q0 - sh_b<R>(c, l, m) * q1;
-      q1 = q0; q0 = qn;
-    }
-  }
-  R n = sh_n<R>(c, J, m) * q0;
-  *yp = n * cr;
-  *ym = n * ci;
-}
-
 // Recurrence state for the eight elements a lane holds, carried across a sequence of
 // harmonics (J, m) visited in order of m, then J: (x + i y)^m in (cr, ci) and Qt_J^m,
 // Qt_{J-1}^m in (q0, q1).  After set_m(m); advance(J) the harmonic of element s is
@@ -465,8 +441,8 @@ struct ShRec8 {
 };
 
 // All y_l^nu for even l <= LMAX (index sh_index(l, nu) - compact even-l layout given by
-// the caller through out[l*l + l + nu] with odd l left untouched); with ODD every l <= LMAX.
-template <typename R, int LMAX, bool ODD = false>
+// the caller through out[l*l + l + nu] with odd l left untouched).
+template <typename R, int LMAX>
 __device__ __forceinline__ void real_sh_even(const ShConst &c, R x, R y, R z, R *out) {
 #pragma unroll
   for (int m = 0; m <= LMAX; ++m) {
@@ -479,7 +455,7 @@ __device__ __forceinline__ void real_sh_even(const ShConst &c, R x, R y, R z, R 
       else if (l == m + 1) q = (R)(2 * m + 1) * z;
       else q = sh_a<R>(c, l, m) * z * q1 - sh_b<R>(c, l, m) * q2;
       if (l > m) { q2 = q1; q1 = q; }
-      if (ODD || (l & 1) == 0) {
+      if ((l & 1) == 0) {
         R n = sh_n<R>(c, l, m) * q;
         out[l * l + l + m] = n * cr;
         if (m > 0) out[l * l + l - m] = n * ci;

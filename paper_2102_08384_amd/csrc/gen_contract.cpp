@@ -92,7 +92,6 @@ bool emit_mid(FILE *f, int L, int K, bool all) {
   int NA = 0;
   for (int l = 2; l <= L; l += 2) NA += 2 * l + 1;
   std::fprintf(f, "template <typename R> struct MidReweight<%d, %d, %s, R> {\n", L, K, all ? "true" : "false");
-  std::fprintf(f, "  static constexpr bool kGenerated = true;\n");
   std::fprintf(f, "  static constexpr int NG = %d, NA = %d, NCH = %d;\n", NG, NA, NCH);
   emit_dirs(f, K, all);
   // chunk -> (Dp index, J1 mu1 index) -> local g index -> [(coef, A index)]: one weighted value at a

@@ -38,14 +38,14 @@ void upload_sh_const_inverse(const ShConst &c) {
 // and an odd field's h is multiplied by i.
 
 // On entry lane t holds v[s] = Z(t + s T); `at` is this pencil's LDS row, free on entry and on exit
-// (the caller's next exchange comes after the closing barrier).  fn(s, z, h_a, h_b) is called for
+// (the caller's next exchange comes after the closing barrier).  fn(z, h_a, h_b) is called for
 // the planes z = t + s T <= zmax of this lane.
 template <typename R, int T, int N, typename At, typename Fn>
 __device__ __forceinline__ void split_half(const cplx<R> v[8], int t, int zmax, At at, Fn fn) {
 #pragma unroll
-  for (int s = 3; s < 8; ++s) {  // mirrors of 1 .. N/2
+  for (int s = 4; s < 8; ++s) {  // mirrors of 1 .. N/2
     const int z = t + s * T;
-    if (z >= N / 2 && N - z <= zmax) at(z) = v[s];
+    if (N - z <= zmax) at(z) = v[s];
   }
   __syncthreads();
 #pragma unroll
@@ -53,7 +53,7 @@ __device__ __forceinline__ void split_half(const cplx<R> v[8], int t, int zmax, 
     const int z = t + s * T;
     if (z <= zmax && z <= N / 2) {
       const cplx<R> w = z == 0 ? v[0] : at(N - z);
-      fn(s, z, mk<R>(v[s].x + w.x, v[s].y - w.y), mk<R>(v[s].y + w.y, w.x - v[s].x));
+      fn(z, mk<R>(v[s].x + w.x, v[s].y - w.y), mk<R>(v[s].y + w.y, w.x - v[s].x));
     }
   }
   __syncthreads();
@@ -98,7 +98,7 @@ k_iz(const R *__restrict__ in, cplx<R> *__restrict__ out, int nfields, int64_t n
     fft_pencil<R, N, true>(v, t, twr, at, sync);
     cplx<R> *oa = out + (size_t)p * nz * npen + q, *ob = oa + (size_t)nz * npen;
     const bool two = p + 1 < nfields;
-    split_half<R, T, N>(v, t, nz - 1, at, [&](int, int z, cplx<R> ha, cplx<R> hb) {
+    split_half<R, T, N>(v, t, nz - 1, at, [&](int z, cplx<R> ha, cplx<R> hb) {
       oa[(size_t)z * npen] = ha;
       if (two) ob[(size_t)z * npen] = hb;
     });
@@ -379,7 +379,7 @@ k_fziz_half(const cplx<R> *__restrict__ in, cplx<R> *__restrict__ out, int nfiel
     fft_pencil<R, N, true>(v, t, twr, at, sync);
     const __amdgpu_buffer_rsrc_t ra = buf_rsrc(out + (size_t)p * nz * npen, out_bytes);
     const __amdgpu_buffer_rsrc_t rb = buf_rsrc(out + (size_t)(p + 1) * nz * npen, out_bytes);
-    split_half<R, T, N>(v, t, nz - 1, at, [&](int, int z, cplx<R> ha, cplx<R> hb) {
+    split_half<R, T, N>(v, t, nz - 1, at, [&](int z, cplx<R> ha, cplx<R> hb) {
       const uint32_t zo = has ? (uint32_t)((z * npen + q) * E) : kOob;
       buf_store<R, store_policy(N)>(odd_a ? mk<R>(-ha.y, ha.x) : ha, ra, zo, 0);
       if (two) buf_store<R, store_policy(N)>(odd_b ? mk<R>(-hb.y, hb.x) : hb, rb, zo, 0);
@@ -711,10 +711,10 @@ static void ix_launch(hipStream_t s, const void *in, int rs, const FieldJob *job
                       const int *bin_of_s2, int64_t n_s2, int nbins, double *acc, const void *tw) {
   constexpr int ROWS = FxShape<N>::ROWS;
   const int64_t nrows = (int64_t)nz * ny;
-  // Few rows lie inside the r-bins of a coarse mesh (about 200 at 128^3 for bins to 200 in a box of 2900:
-  // 24 workgroups), each a chain over every job: the jobs are shared out over grid y until a thousand
-  // workgroups run, at least three jobs each: with 28 targets 80 -> 30 us.  At 512^3 the rows alone fill the chip (640 workgroups of two waves per SIMD) and
-  // sharing them out three ways was slower (1.22 -> 1.27 ms).
+  // Few rows lie inside the r-bins of a coarse mesh (9 x 17 at 128^3 for bins to 200 in a box of 2900:
+  // 20 workgroups), each a chain over every job: the jobs are shared out over grid y until a thousand
+  // workgroups run, at least three jobs each: with 28 targets 80 -> 30 us.  At 512^3 the rows alone fill the
+  // chip (640 workgroups of two waves per SIMD) and sharing them out three ways was slower (1.22 -> 1.27 ms).
   const unsigned nblk = (unsigned)((nrows + ROWS - 1) / ROWS);
   dim3 grid(nblk, std::max(1u, std::min(1024u / nblk, (unsigned)njobs / 3u)));
   const size_t sh = (size_t)(nell + 2) * nbins * sizeof(double);

@@ -135,14 +135,10 @@ k_fx(const R *__restrict__ mesh, cplx<R> *__restrict__ out, const FieldJob *__re
   const int rl = threadIdx.x / T, t = threadIdx.x % T;
   // row = z * N + y: every row (grid covers N*N exactly), or the non-empty rows in order
   int row = blockIdx.x * ROWS + rl;
-  bool live = true;
   if (rowlist) {
-    const int nr = norm->nrows_occ;
-    if ((int)blockIdx.x * ROWS >= nr) return;  // uniform for the block: before any barrier
-    live = row < nr;
-    row = live ? rowlist[row] : 0;
+    if (row >= norm->nrows_occ) return;  // (whole groups of T lanes, and no block-wide barrier follows)
+    row = rowlist[row];
   }
-  if (!live) return;  // (whole groups of T lanes, and no block-wide barrier follows)
   const int y = row & (N - 1), z = row / N;
   const int partner = (threadIdx.x & 63 & ~(T - 1)) | ((T - t) & (T - 1));  // lane T - t of the row
   cplx<R> *my = lds + rl * LN;
@@ -162,7 +158,7 @@ k_fx(const R *__restrict__ mesh, cplx<R> *__restrict__ out, const FieldJob *__re
   };
 #pragma unroll
   for (int s = 0; s < 8; ++s) {
-    f[s] = live ? mesh[(size_t)row * N + t + s * T] : (R)0;
+    f[s] = mesh[(size_t)row * N + t + s * T];
     const R ir = inv_r(s);
     g[s] = RADIAL ? ir : (ir > (R)0 ? pz * ir : (R)1);
   }

@@ -13,9 +13,7 @@
 
 namespace pw {
 
-template <int L, int K, bool ALLP, typename R> struct MidReweight {
-  static constexpr bool kGenerated = false;
-};
+template <int L, int K, bool ALLP, typename R> struct MidReweight;
 #include "mix_gen.inc"
 
 // A workgroup holds one cell per thread: NT / N rows (z, y), N <= 256, or one row of 512.  The g

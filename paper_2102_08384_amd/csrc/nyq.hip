@@ -10,9 +10,7 @@
 
 namespace pw {
 
-template <int L, int K, bool ALLP, typename R> struct MidReweight {
-  static constexpr bool kGenerated = false;
-};
+template <int L, int K, bool ALLP, typename R> struct MidReweight;
 #include "mix_gen.inc"
 
 // Row (p, z) of nyy (half spectrum along x) to real space, N/8 lanes each
