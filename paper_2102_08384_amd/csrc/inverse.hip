@@ -593,7 +593,11 @@ k_ix(const cplx<R> *__restrict__ in, int rs, const FieldJob *__restrict__ jobs, 
   // geometry of the eight cells this lane holds
   R ux[8], uy[8], uz[8], dm[8];
   int bin[8];
-  R X[kMaxEll][8];
+  // The sums over the jobs run in FP64: in FP32 their rounding is the largest of the inverse passes, and half
+  // of the separations average it half as often as all would (FP32 error of xi_2, all-parity order 4 at
+  // 128^3, against FP64: all planes 1.9e-7 of |xi_0|, half with FP32 sums 4.3e-7, this 1.1e-7).  The kernel runs one
+  // wave per SIMD either way (256 VGPRs); 512^3: 0.73 ms with both.
+  double X[kMaxEll][8];
   const int nacc = (nell + 2) * nbins;
   for (int i = threadIdx.x; i < nacc; i += blockDim.x) bacc[i] = 0.0;
 #pragma unroll
@@ -679,7 +683,7 @@ k_ix(const cplx<R> *__restrict__ in, int rs, const FieldJob *__restrict__ jobs, 
       if (l < nell) {
         const R fa = ca[l], fb = cb[l];
 #pragma unroll
-        for (int s = 0; s < 8; ++s) X[l][s] += fa * ya[s] * v[s].x + fb * yb[s] * v[s].y;
+        for (int s = 0; s < 8; ++s) X[l][s] += (double)(fa * ya[s]) * v[s].x + (double)(fb * yb[s]) * v[s].y;
       }
     }
   }
@@ -694,7 +698,7 @@ k_ix(const cplx<R> *__restrict__ in, int rs, const FieldJob *__restrict__ jobs, 
     const double s2 = (double)sx * sx + (double)sy * sy + (double)sz * sz;
 #pragma unroll
     for (int l = 0; l < kMaxEll; ++l)
-      if (l < nell) atomicAdd(&bacc[l * nbins + b], mult * (double)(X[l][s] * scale));
+      if (l < nell) atomicAdd(&bacc[l * nbins + b], mult * X[l][s] * (double)scale);
     if (blockIdx.y == 0) {  // each cell is counted once
       atomicAdd(&bacc[nell * nbins + b], mult);
       atomicAdd(&bacc[(nell + 1) * nbins + b], mult * Hd * sqrt(s2));
