@@ -533,11 +533,11 @@ size_t table_bytes(const HostPlan &h) {
              (h.fwd.goff.size() + h.sph.goff.size() + h.fwd.yoff.size() +
               h.sph.yoff.size() + h.iyoff.size()) * 8 +
              (h.fwd.ycnt.size() + h.sph.ycnt.size() + h.fwd.gsize.size() + h.sph.gsize.size() + h.zrank.size() +
-              h.zidx.size() + h.yidx.size() + h.iycnt.size() + h.odd_of.size()) * 4;
+              h.zidx.size() + h.yidx.size() + h.iycnt.size()) * 4;
   b += (h.t_start.size() + h.t_sh.size() + h.t_ell.size() + h.t_p1.size() + h.t_p2.size()) * 4 +
        (h.t_coef.size() + h.winv.size() + h.icoef.size()) * rsz;
   b += (size_t)nt * nt * nt * 16 + (size_t)h.N * h.N * 8 + (size_t)h.N * 8;  // tile sort, occupancy
-  return b + ((size_t)1 << 20);  // job lists, twiddles, result rows and scalars
+  return b + ((size_t)1 << 20);  // lists of jobs and of fields, twiddles, result rows and scalars
 }
 
 size_t plan_bytes(const pw_config &c) {
