@@ -135,10 +135,14 @@ k_fx(const R *__restrict__ mesh, cplx<R> *__restrict__ out, const FieldJob *__re
   const int rl = threadIdx.x / T, t = threadIdx.x % T;
   // row = z * N + y: every row (grid covers N*N exactly), or the non-empty rows in order
   int row = blockIdx.x * ROWS + rl;
+  bool live = true;
   if (rowlist) {
-    if (row >= norm->nrows_occ) return;  // (whole groups of T lanes, and no block-wide barrier follows)
-    row = rowlist[row];
+    const int nr = norm->nrows_occ;
+    if ((int)blockIdx.x * ROWS >= nr) return;  // uniform for the block: before any barrier
+    live = row < nr;
+    row = live ? rowlist[row] : 0;
   }
+  if (!live) return;  // (whole groups of T lanes, and no block-wide barrier follows)
   const int y = row & (N - 1), z = row / N;
   const int partner = (threadIdx.x & 63 & ~(T - 1)) | ((T - t) & (T - 1));  // lane T - t of the row
   cplx<R> *my = lds + rl * LN;
