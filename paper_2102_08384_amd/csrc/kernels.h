@@ -106,12 +106,13 @@ void launch_sort_count(hipStream_t s, const SortLayout &L, const void *gx, int g
                        const void *rnbar, int64_t ng, int64_t nr, int N, const double *b0, double H, int assign,
                        int *chunk_hist, int *counts, double *part_g, double *part_r);
 // Tiles painted by several workgroups.  `mem` (memory that is free during the paint) holds, written by the
-// scan, the numbers of whole tiles and of parts and a list of both, the whole tiles first: the tile's slot,
-// its first part's index among the parts, its first record and its records; behind the list an int64 block
-// for each part.  per: records of a part (0: every tile by one workgroup, no list); most: parts at most.
+// scan, the numbers of whole tiles and of parts, the records of a part and a list of both kinds, the whole
+// tiles first: the tile's slot, its first part's index among the parts, its first record and its records;
+// behind the list an int64 block for each part.  per: records of a part at least (0: every tile by one
+// workgroup, no list); most: parts at most; room: the blocks that fit, where that limits the parts (else 0).
 struct PaintCut {
   static constexpr int kMost = 1024;
-  int per = 0, most = 0, list_bytes = 0;
+  int per = 0, most = 0, room = 0, list_bytes = 0;
   void *mem = nullptr;
   __device__ int *head() const { return (int *)mem; }
   __device__ int4 *entry() const { return (int4 *)((char *)mem + 256); }

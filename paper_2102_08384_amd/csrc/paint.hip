@@ -294,7 +294,7 @@ __device__ void tile_scan(const int *__restrict__ counts, int ntiles, int *__res
                           int *__restrict__ slot, const PaintCut cut) {
   __shared__ int part[1024];
   __shared__ int occ[1024];
-  __shared__ int lst[1024];
+  __shared__ int lst[16];
   const int per = (ntiles + 1023) / 1024;
   const int b = threadIdx.x * per, e = min(ntiles, b + per);
   const bool vec = (ntiles % 4096) == 0 && per <= 64;
@@ -317,28 +317,15 @@ __device__ void tile_scan(const int *__restrict__ counts, int ntiles, int *__res
       o += counts[i] > 0;
     }
   }
-  // (tiles are cut on meshes of 1, 8, 64, 512 or 4096 tiles: runs of one tile, or vectors of four)
-  const int len[4] = {vec ? c[0] : s, vec ? c[1] : 0, vec ? c[2] : 0, vec ? c[3] : 0};
-  int np[4] = {0, 0, 0, 0}, l = 0;  // l: parts of this run's cut tiles, and from bit 16 the number of those tiles
-  if (cut.per > 0) {  // uniform
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      np[k] = tile_parts(len[k], cut.per);
-      if (np[k] > 1) l += np[k] + 0x10000;
-    }
-  }
   part[threadIdx.x] = s;
   occ[threadIdx.x] = o;
-  lst[threadIdx.x] = l;
   __syncthreads();
   for (int off = 1; off < 1024; off <<= 1) {  // inclusive Hillis-Steele scans
     int v = (int)threadIdx.x >= off ? part[threadIdx.x - off] : 0;
     int w = (int)threadIdx.x >= off ? occ[threadIdx.x - off] : 0;
-    int u = (int)threadIdx.x >= off ? lst[threadIdx.x - off] : 0;
     __syncthreads();
     part[threadIdx.x] += v;
     occ[threadIdx.x] += w;
-    lst[threadIdx.x] += u;
     __syncthreads();
   }
   int run = threadIdx.x > 0 ? part[threadIdx.x - 1] : 0;
@@ -367,9 +354,34 @@ __device__ void tile_scan(const int *__restrict__ counts, int ntiles, int *__res
     offsets[ntiles] = part[1023];
     slot[ntiles] = occ[1023];
   }
-  if (cut.per > 0) {
-    const int before = threadIdx.x > 0 ? lst[threadIdx.x - 1] : 0;
-    const int whole = occ[1023] - (lst[1023] >> 16);
+  if (cut.per > 0) {  // uniform
+    // records of a part: where room is short, so many that the parts fit: fewer than total / pp of them
+    // and one more for every occupied tile
+    const int total = part[1023], nocc = occ[1023], free = cut.room - nocc;
+    const int pp = cut.room == 0 ? cut.per : free > 0 ? max(cut.per, (total + free - 1) / free) : total;
+    // (tiles are cut on meshes of 1, 8, 64, 512 or 4096 tiles: runs of one tile, or vectors of four)
+    const int len[4] = {vec ? c[0] : s, vec ? c[1] : 0, vec ? c[2] : 0, vec ? c[3] : 0};
+    int np[4], l = 0;  // l: parts of this run's cut tiles, and from bit 16 the number of those tiles
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      np[k] = tile_parts(len[k], pp);
+      if (np[k] > 1) l += np[k] + 0x10000;
+    }
+    const int lane = threadIdx.x & 63, wv = threadIdx.x / 64;
+    int incl = l;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int u = __shfl_up(incl, off);
+      if (lane >= off) incl += u;
+    }
+    if (lane == 63) lst[wv] = incl;
+    __syncthreads();
+    int before = incl - l, all = 0;
+    for (int k = 0; k < 16; ++k) {
+      if (k < wv) before += lst[k];
+      all += lst[k];
+    }
+    const int whole = nocc - (all >> 16);
     int beg = threadIdx.x > 0 ? part[threadIdx.x - 1] : 0, rank = threadIdx.x > 0 ? occ[threadIdx.x - 1] : 0;
     int w = rank - (before >> 16), first = before & 0xffff;
 #pragma unroll
@@ -386,7 +398,8 @@ __device__ void tile_scan(const int *__restrict__ counts, int ntiles, int *__res
     }
     if (threadIdx.x == 1023) {
       cut.head()[0] = whole;
-      cut.head()[1] = lst[1023] & 0xffff;
+      cut.head()[1] = all & 0xffff;
+      cut.head()[2] = pp;
     }
   }
 }
@@ -516,7 +529,7 @@ __global__ void __launch_bounds__(512) k_tile_paint(int ts, const int *__restric
     whole = uniform(cut.head()[0]);
     if ((int)blockIdx.x >= whole + uniform(cut.head()[1])) return;
     at = uniform(e.x); beg0 = uniform(e.z); len = uniform(e.w);
-    np = tile_parts(len, cut.per);
+    np = tile_parts(len, uniform(cut.head()[2]));
     if (np > 1) part = (int)blockIdx.x - whole - uniform(e.y);
   } else {
     const int tile = blockIdx.x;
@@ -598,7 +611,7 @@ __global__ void __launch_bounds__(256) k_tile_combine(int ts, const DevNorm *__r
                                                       RM *__restrict__ blocks) {
   if ((int)blockIdx.x >= cut.head()[1]) return;  // uniform
   const int4 e = cut.entry()[cut.head()[0] + blockIdx.x];
-  const int np = tile_parts(e.w, cut.per);
+  const int np = tile_parts(e.w, cut.head()[2]);
   const int E = ts + 2, E3 = E * E * E;
   const double inv = 1.0 / (sizeof(RM) == 4 ? norm->fix_scale * (1.0 / 2048.0) : norm->fix_scale);
   const long long *src = cut.blocks() + (size_t)e.y * E3;
@@ -924,12 +937,14 @@ static int ilog2(int v) {
 // cost about as much as depositing 1000) and a 512th of the catalog (two workgroups per CU in all:
 // with a 2048-record limit alone, 10^3 occupied tiles of 6 10^3 records were cut in three and the
 // stage went from 0.40 to 0.50 ms).  So there are at most 2 n / per parts: fewer than n / per tiles
-// hold more than `per`, and each adds one to its share of n / per.  Paint stage, whole tiles -> this: 6 10^6
+// hold more than `per`, and each adds one to its share of n / per; scratch with less room than that (a few
+// fields on a small mesh) gets larger parts, for the tiles that are occupied.  Paint stage, whole tiles -> this: 6 10^6
 // particles of a survey in a doubled 256^3 box 0.52 -> 0.25 ms, 1.5 10^6 at 128^3 0.148 -> 0.113 ms.
 // Whole tiles on meshes whose tiles outnumber the CUs many times, and for catalogs too thin to fill
 // parts (128^3, 3.6 10^5 particles, whole estimates: 170 us whole tiles, 178 in parts; 1.65 10^6: 290 and
 // 279).  The work comes from a list, so where no tile is crowded only the list and some empty workgroups are
-// added: 6 10^6 particles evenly in a 256^3 box 0.336 -> 0.345 ms (a grid of tiles times parts: 0.37 ms).
+// added: 6 10^6 particles evenly in a 256^3 box take 0.337 ms, with or without (a grid of tiles times parts:
+// 0.36 ms).  Short room: 3 10^5 particles in 8 tiles at 64^3, monopole alone, 0.198 -> 0.100 ms.
 PaintCut paint_cut(int N, int64_t n_part, void *scratch, size_t scratch_bytes) {
   PaintCut cut;
   const int ts = tile_size(N);
@@ -938,10 +953,11 @@ PaintCut paint_cut(int N, int64_t n_part, void *scratch, size_t scratch_bytes) {
   const size_t E3 = (size_t)(ts + 2) * (ts + 2) * (ts + 2);
   const int64_t list = (256 + (ntiles + PaintCut::kMost) * (int64_t)sizeof(int4) + 255) / 256 * 256;
   const int64_t room = ((int64_t)scratch_bytes - list) / (int64_t)(E3 * sizeof(long long));
-  const int64_t n = std::min({(int64_t)PaintCut::kMost / 2, n_part / 2048, room / 2});
-  if (n < 32) return cut;  // (no room for parts small enough to matter)
+  const int64_t n = std::min((int64_t)PaintCut::kMost / 2, n_part / 2048);
+  if (room < 2) return cut;
   cut.per = (int)std::max<int64_t>(2048, (n_part + n - 1) / n);
-  cut.most = (int)(2 * n);
+  cut.most = (int)std::min(2 * n, room);
+  cut.room = room < 2 * n ? (int)room : 0;
   cut.list_bytes = (int)list;
   cut.mem = scratch;
   return cut;
